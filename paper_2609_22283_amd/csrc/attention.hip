@@ -48,42 +48,143 @@ struct AttnGeom {
 };
 
 // ------------------------------------------------------------- fp32 kernel
-// One thread per query row, keys streamed from the cache; used for the fp32
-// path (small parity shapes), not tuned.
+// Work-group: 16 queries of one (node, head).  Its eight waves take eight
+// contiguous parts of the node's key tiles (16 keys of one page), each with
+// its own online softmax, and merge through LDS at the end, in a fixed order
+// and without a workspace.  Both products run on 16x16x4 fp32 MFMAs; their
+// operands come straight from the cache as 16-byte loads (fp32 data is only
+// 4-byte aligned, which is all these loads need):
+//   S^T = K Q^T   the contraction index of MFMA (j, e) in lane group g is
+//                 channel 16 j + 4 g + e, so a lane reads runs of 4 channels
+//                 of its key row, and of its query row
+//   O^T += V^T P^T  MFMA e contracts keys 4 g + e of the tile: lane (g, c)'s
+//                 result e of S^T is then its B operand as it stands, and
+//                 the A operand a run of 4 tokens of one V^T row
+// What bounds it: the fp32 matrix rate of the compute units that hold
+// work-groups (a 16-key tile is 64 MFMAs of 32 cycles at head_dim 128), and
+// at few tiles per wave the loads' latency.  The split over waves fills the
+// chip from one node's queries: one thread per query (the form before) had
+// 40 waves in flight and a chain of 128 dependent FMAs per key.
+// 4 nodes x 312 queries x 2184 keys, 2 heads of 128: 59 us (47 TFLOP/s) against
+// 15.6 ms.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int F32_NW = 8, F32_BQ = 16, F32_BK = 16;
+
 template <int HD>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ o,
-                                                      AttnGeom g, AttnPlan plan) {
-  const uint32_t qt_n = (g.nq + 63) / 64;
-  const uint32_t w = blockIdx.x;
-  const int32_t qt = w % qt_n;
-  const int32_t node = (w / qt_n) % g.n_nodes;
-  const int32_t head = w / (qt_n * g.n_nodes);
-  const int32_t row = qt * 64 + threadIdx.x;
-  if (row >= g.nq) return;
-  const size_t qoff = (((size_t)node * g.nq + row) * g.n_heads + head) * HD;
-  float qr[HD], acc[HD];
-  for (int d = 0; d < HD; ++d) {
-    qr[d] = q[qoff + d] * g.scale;
-    acc[d] = 0.f;
+__global__ __launch_bounds__(64 * F32_NW) void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ o,
+                                                               AttnGeom g, AttnPlan plan) {
+  constexpr int NJ = HD / 16;  // 16-channel blocks
+  __shared__ f32x4 part[F32_NW / 2][NJ][64];
+  __shared__ float ml[2][F32_NW][F32_BQ];
+  const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t lg = lane >> 4, c = lane & 15;
+  // query tiles fastest: an XCD's work-groups share the K/V of one or two (node, head)s
+  const int32_t unit = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
+  const int32_t qt = unit % g.n_qtiles, nh = unit / g.n_qtiles;
+  const int32_t node = nh % g.n_nodes, head = nh / g.n_nodes;
+  const int32_t row = qt * F32_BQ + c;
+  const size_t qoff = (((size_t)node * g.nq + min(row, g.nq - 1)) * g.n_heads + head) * HD + 4 * lg;
+  f32x4 qr[NJ], acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    qr[j] = *reinterpret_cast<const f32x4u*>(q + qoff + 16 * j) * g.scale;
+    acc[j] = f32x4{};
   }
+  const int32_t p0 = plan.page_off[node], npages = plan.page_off[node + 1] - p0;
+  const int32_t tp = (g.tpp + F32_BK - 1) / F32_BK, nt = npages * tp;  // tiles per page, in all
+  const int32_t t_end = (int32_t)((int64_t)(wave + 1) * nt / F32_NW);
+  int32_t t = (int32_t)((int64_t)wave * nt / F32_NW), page = t / tp, tt = t - page * tp;
+  // K rows of keys past the page's end read its last key, V^T runs past it
+  // the page's first tokens (valid memory; their probabilities are zero)
+  auto load_k = [&](f32x4 (&kf)[NJ]) {
+    const float* kb = reinterpret_cast<const float*>(g.layer_base + (size_t)plan.page_slot[p0 + page] * g.slot_bytes) +
+                      ((size_t)head * g.tpp + min(F32_BK * tt + c, g.tpp - 1)) * HD + 4 * lg;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) kf[j] = *reinterpret_cast<const f32x4u*>(kb + 16 * j);
+  };
   float m = -INFINITY, l = 0.f;
-  for (int32_t p = plan.page_off[node]; p < plan.page_off[node + 1]; ++p) {
-    const char* base = g.layer_base + (size_t)plan.page_slot[p] * g.slot_bytes;
-    const float* kb = reinterpret_cast<const float*>(base) + (size_t)head * g.tpp * HD;
-    const float* vb = reinterpret_cast<const float*>(base + g.kv_half) + (size_t)head * HD * g.tpp;
-    for (int32_t t = 0; t < g.tpp; ++t) {
-      float s = 0.f;
-      for (int d = 0; d < HD; ++d) s = fmaf(qr[d], kb[(size_t)t * HD + d], s);
-      const float mn = fmaxf(m, s);
-      const float alpha = expf(m - mn);
-      const float pr = expf(s - mn);
-      l = l * alpha + pr;
-      for (int d = 0; d < HD; ++d) acc[d] = fmaf(pr, vb[(size_t)d * g.tpp + t], acc[d] * alpha);
+  f32x4 kf[NJ];
+  if (t < t_end) load_k(kf);
+  while (t < t_end) {
+    const int32_t k0 = F32_BK * tt + 4 * lg;  // this lane's first key of the tile, within the page
+    f32x4 vf[NJ];
+    {
+      const float* vb = reinterpret_cast<const float*>(g.layer_base + (size_t)plan.page_slot[p0 + page] * g.slot_bytes +
+                                                       g.kv_half) +
+                        ((size_t)head * HD + c) * g.tpp + (k0 < g.tpp ? k0 : 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) vf[j] = *reinterpret_cast<const f32x4u*>(vb + (size_t)16 * j * g.tpp);
+    }
+    f32x4 s0 = {}, s1 = {};
+#pragma unroll
+    for (int j = 0; j < NJ; j += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qr[j][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qr[j + 1][e], s1, 0, 0, 0);
+      }
+    ++t;
+    if (++tt == tp) {
+      tt = 0;
+      ++page;
+    }
+    if (t < t_end) load_k(kf);
+    f32x4 s = s0 + s1;
+    if (k0 + 4 > g.tpp) s = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // pages hold whole runs of 8 keys
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mn = fmaxf(m, mx);
+    if (__builtin_amdgcn_ballot_w64(mn > m)) {
+      const float alpha = mn == -INFINITY ? 1.f : expf(m - mn);
+      l *= alpha;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[j] *= alpha;
       m = mn;
     }
+    const float ms = m == -INFINITY ? 0.f : m;  // every logit so far -inf: no weight yet
+    f32x4 p;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[e] = expf(s[e] - ms);
+    l += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[j][e], p[e], acc[j], 0, 0, 0);
   }
-  const float inv = 1.f / l;
-  for (int d = 0; d < HD; ++d) o[qoff + d] = acc[d] * inv;
+  // merge: every wave scales its part to the common maximum, then a tree of
+  // LDS additions (a wave without tiles adds zeros)
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (lg == 0) {
+    ml[0][wave][c] = m;
+    ml[1][wave][c] = l;
+  }
+  __syncthreads();
+  float mt = ml[0][0][c], lt = 0.f;
+#pragma unroll
+  for (int w = 1; w < F32_NW; ++w) mt = fmaxf(mt, ml[0][w][c]);
+#pragma unroll
+  for (int w = 0; w < F32_NW; ++w) lt += ml[1][w][c] * expf(ml[0][w][c] - mt);
+  const float f = expf(m - mt);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) acc[j] *= f;
+#pragma unroll
+  for (int h = F32_NW / 2; h >= 1; h /= 2) {
+    if (wave >= h && wave < 2 * h)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) part[wave - h][j][lane] = acc[j];
+    __syncthreads();
+    if (wave < h)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[j] += part[wave][j][lane];
+    __syncthreads();
+  }
+  if (wave == 0 && row < g.nq) {
+    const float inv = 1.f / lt;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) *reinterpret_cast<f32x4u*>(o + qoff + 16 * j) = acc[j] * inv;
+  }
 }
 
 // ------------------------------------------------------------- bf16 kernel
@@ -1162,14 +1263,14 @@ static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t 
   g.scale = scale;
   g.scale_log2 = scale * 1.4426950408889634f;
   if (d.dtype == SC_DTYPE_F32) {
-    g.n_qtiles = (p->nq + 63) / 64;
+    g.n_qtiles = (p->nq + F32_BQ - 1) / F32_BQ;
     const uint32_t nwg = (uint32_t)n * d.n_heads * g.n_qtiles;
     timer_begin(TK_ATTENTION, stream);
     if (d.head_dim == 64)
-      hipLaunchKernelGGL((attn_f32_kernel<64>), dim3(nwg), dim3(64), 0, stream,
+      hipLaunchKernelGGL((attn_f32_kernel<64>), dim3(nwg), dim3(64 * F32_NW), 0, stream,
                          static_cast<const float*>(q), static_cast<float*>(o), g, plan);
     else
-      hipLaunchKernelGGL((attn_f32_kernel<128>), dim3(nwg), dim3(64), 0, stream,
+      hipLaunchKernelGGL((attn_f32_kernel<128>), dim3(nwg), dim3(64 * F32_NW), 0, stream,
                          static_cast<const float*>(q), static_cast<float*>(o), g, plan);
     timer_end(TK_ATTENTION, stream);
     SC_HIP(hipGetLastError());
