@@ -144,6 +144,13 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   uint16_t* xb = static_cast<uint16_t*>(x);
   const int32_t D = w->hidden;
 
+  // The attention's workspace also holds the partial sums of GEMMs whose
+  // contraction is split: no GEMM runs while the attention uses it.
+  auto scratch = [&](GemmEpilogue& e) {
+    e.part = reinterpret_cast<float*>(attn_ws);
+    e.part_bytes = attention_workspace_bound();
+  };
+  scratch(ep);
   ep.q_out = qb;
   ep.layer_base = c->pool + (size_t)layer * d.n_slots * c->slot_bytes;
   ep.slot_bytes = c->slot_bytes;
@@ -209,6 +216,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     return rc;
   GemmEpilogue e2;
   std::memset(&e2, 0, sizeof e2);
+  scratch(e2);
   e2.out = xb;
   e2.ld_out = D;
   e2.nq = p->nq;
@@ -231,6 +239,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     if ((rc = launch_row_rms(xb, T, D, rsq, stream)) != SC_OK) return rc;
     GemmEpilogue ec;
     std::memset(&ec, 0, sizeof ec);
+    scratch(ec);
     ec.out = qb;
     ec.ld_out = D;
     ec.row_scale = rsq;
@@ -260,6 +269,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     }
     GemmEpilogue eo;
     std::memset(&eo, 0, sizeof eo);
+    scratch(eo);
     eo.out = xb;
     eo.ld_out = D;
     eo.nq = p->nq;
@@ -269,6 +279,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   }
   GemmEpilogue e3;
   std::memset(&e3, 0, sizeof e3);
+  scratch(e3);
   e3.out = ub;
   e3.ld_out = w->mlp;
   const uint16_t* mlp_in = hn;

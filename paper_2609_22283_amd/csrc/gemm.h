@@ -50,6 +50,10 @@ struct GemmEpilogue {
   float* ss_part;
   int32_t n_part;
   const float* qk_gain;
+  // Scratch for the partial sums of a contraction split over work-groups
+  // (16-byte aligned); NULL or too small: no split.
+  float* part;
+  size_t part_bytes;
 };
 
 // Second half of an RMSNorm whose sums of squares came from a GEMM epilogue:

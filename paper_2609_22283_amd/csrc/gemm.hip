@@ -15,10 +15,20 @@
 // 64 features, the first half of an RMSNorm over the feature axis (qk-norm);
 // norm_scale_kernel finishes it.  RESIDUAL can emit them for the rows it
 // writes, part-major; row_scale_kernel turns them into a row_scale.
-// Work-group tile 256 (features) x BN (tokens: 256, 224, 192 or 128) x 64
-// (k), eight waves (2 x 4 of 128 x BN/4, or 4 x 2 of 64 x BN/2 at 224),
-// operands double-buffered in LDS with an XOR swizzle.  Each lane holds four consecutive features of one token, so RoPE
-// pairs stay in-lane.
+// Work-groups take tiles of the output (seven shapes, 256 x 256 down to
+// 64 x 64) and, where the tiles alone would leave CUs idle, parts of the
+// contraction too; the parts' fp32 sums meet in gemm_reduce_kernel, which adds
+// them in order and runs the epilogue.  Operands go through an LDS ring of
+// 64-k stages with an XOR swizzle.  Each lane holds four consecutive features
+// of one token, so RoPE pairs stay in-lane.
+//
+// What bounds it: at thousands of tokens the matrix cores' issue and the
+// ring's copies (MLP-down at 18720 tokens 1.15 PFLOP/s, 450 us, against 480 us
+// before fragments were read ahead across the stage barrier); at a few
+// hundred tokens the copies' latency and the launch, since the weights are
+// read once.  Before the small tiles and the split, launches of 64 .. 512
+// tokens took 26 - 35 us at 1536 k and 120 us at 8960 k whatever their size (6
+// to 70 work-groups, one 48 KB stage in flight each); now 8 - 20 us.
 #include <cstring>
 
 #include "device.h"
@@ -27,12 +37,8 @@
 
 namespace sc {
 
-constexpr int GBM = 256, GBK = 64;
-constexpr int GWM = 128;
-constexpr int G_NW = 8;               // waves per work-group, two per SIMD
-constexpr int G_THREADS = 64 * G_NW;
-constexpr int GROWS = GBM / G_NW;     // weight rows each wave copies per stage
-constexpr int G_TILE_BYTES = GBM * GBK * 2;  // 32 KB per operand per stage
+constexpr int GBM = 256;  // features come in multiples of the widest tile
+constexpr int GBK = 64;   // k of one LDS stage
 
 // GELU_tanh(x) = 0.5 x (1 + tanh(u)) = x * sigmoid(2 u), u = sqrt(2/pi) (x + 0.044715 x^3),
 // evaluated as x / (1 + 2^(-2 u log2 e)).
@@ -41,25 +47,6 @@ __device__ __forceinline__ float gelu_tanh(float x) {
   const float q = x * fmaf(x * x, -k * 0.044715f, -k);
   const float e = __builtin_amdgcn_exp2f(q);
   return x * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
-// Direct global -> LDS copy of 16 bytes per lane (lane i lands at LDS base
-// + 16 i) from base + off.  Written as inline asm: while a copy it knows of
-// is in flight, the compiler waits for every LDS fragment read with
-// lgkmcnt(0); not knowing of these, it counts the reads exactly (the copies
-// complete under the loop's explicit vmcnt(0) wait).  M0, which carries the
-// LDS address, is saved and restored.  (QKV and MLP-up GEMMs 2 % faster.)
-__device__ __forceinline__ void gdma16(const char* base, uint32_t off, char* lds_wave_base) {
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(off), "s"(base), "s"((uint32_t)reinterpret_cast<uintptr_t>(lds_wave_base))
-      : "memory");
 }
 
 // Per-token sums of squares of a wave's accumulator tile, one partial per
@@ -88,164 +75,59 @@ __device__ __forceinline__ void store_sum_squares(const f32x4 (&acc)[FB][TB], fl
     }
 }
 
-// BN tokens per work-group tile.  Wave layout WL = 0: 2 (features) x 4
-// (tokens) waves of 128 x BN/4 (BN a multiple of 64; required by the QKV
-// epilogue and the sums of squares, which take one head of 128 features per
-// wave); WL = 1: 4 x 2 waves of 64 x BN/2 (BN a multiple of 32, e.g. 224).
-template <int EPI, int BN, int WL>
-__global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t* __restrict__ W,
-                                                                 const uint16_t* __restrict__ X,
-                                                                 int32_t F, int32_t T, int32_t Kd,
-                                                                 GemmEpilogue ep) {
-  // stage s: W tile at s * 64 KB, X tile at s * 64 KB + 32 KB; rows of 64 k
-  // (128 B) with 16-byte column c stored at c ^ ((row >> 1) & 7)
-  __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * G_TILE_BYTES];
-  constexpr int WM = WL ? 64 : GWM;    // features per wave tile
-  constexpr int GWN = WL ? BN / 2 : BN / 4;  // tokens per wave tile
-  static_assert(GWN % 16 == 0, "wave tiles hold whole 16-token blocks");
-  const int32_t n_tf = F / GBM, n_tt = (T + BN - 1) / BN;
-  // Each XCD takes a contiguous run of logical tiles; the run is walked in
-  // groups of GT token tiles, feature tiles outermost within a group, so the
-  // ~32 tiles an XCD holds at once share 4-5 weight and 8 token panels in L2.
-  constexpr int32_t GT = 8;
-  const int32_t tile = (int32_t)xcd_remap(blockIdx.x, (uint32_t)(n_tf * n_tt));
-  const int32_t group = tile / (GT * n_tf), in_group = tile - group * GT * n_tf;
-  const int32_t gt = min(GT, n_tt - group * GT);
-  const int32_t tf = in_group / gt, tt = group * GT + in_group % gt;
-  const int32_t f0 = tf * GBM, t0 = tt * BN;
-
-  const int32_t tid = threadIdx.x, lane = tid & 63;
-  const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS copy addresses stay scalar
-  const int32_t lg = lane >> 4, c16 = lane & 15;
-  const int32_t wf = WL ? (wave & 3) * WM : (wave & 1) * WM;
-  const int32_t wt = WL ? (wave >> 2) * GWN : (wave >> 1) * GWN;
-
-  // copies: each wave moves weight rows [GROWS wave, GROWS wave + GROWS) and
-  // the 8-row token groups wave, wave + 8, ... (BN / 8 groups in all), 8 rows
-  // (1 KB) per instruction; lane (row, p) fetches column p ^ ((row >> 1) & 7).
-  // Byte offsets are fixed per lane; the k offset is folded into the
-  // (wave-uniform) base pointer.
-  constexpr int NCP = GROWS / 8, XGROUPS = BN / 8, NCPX = (XGROUPS + G_NW - 1) / G_NW;
-  static_assert(BN % 32 == 0 && BN <= GBM && NCPX <= NCP, "token copies ride with the weight copies");
-  uint32_t woff[NCP], xoff[NCPX];
-#pragma unroll
-  for (int j = 0; j < NCP; ++j) {
-    const int32_t row = GROWS * wave + 8 * j + (lane >> 3);
-    const int32_t col = (lane & 7) ^ ((row >> 1) & 7);
-    woff[j] = ((uint32_t)(f0 + row) * Kd + col * 8) * 2;
-  }
-#pragma unroll
-  for (int j = 0; j < NCPX; ++j) {
-    const int32_t row = 8 * min(wave + G_NW * j, XGROUPS - 1) + (lane >> 3);
-    const int32_t col = (lane & 7) ^ ((row >> 1) & 7);
-    const int32_t trow = min(t0 + row, T - 1);
-    xoff[j] = ((uint32_t)trow * Kd + col * 8) * 2;
-  }
-  const char* wbase = reinterpret_cast<const char*>(W);
-  const char* xbase = reinterpret_cast<const char*>(X);
-  auto issue = [&](int32_t k0, int buf) {
-    char* a = smem + buf * 2 * G_TILE_BYTES;
-    char* b = a + G_TILE_BYTES;
-    const char* wk = wbase + (size_t)k0 * 2;
-    const char* xk = xbase + (size_t)k0 * 2;
-#pragma unroll
-    for (int j = 0; j < NCP; ++j) {
-      gdma16(wk, woff[j], a + (GROWS * wave + 8 * j) * 128);
-      if (j < NCPX && (XGROUPS % G_NW == 0 || wave + G_NW * j < XGROUPS))  // wave-uniform
-        gdma16(xk, xoff[j], b + (8 * (wave + G_NW * j)) * 128);
-    }
-  };
-  auto landed = [&]() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  };
-
-  // LDS read offsets of this lane's fragments (16-byte column 4 s + lg)
-  // 16x16x32 MFMAs: lane (lg, c16) supplies row c16 of each 16-row operand
-  // block with k values 8 lg .. 8 lg + 7 of a 32-k step
-  constexpr int FB = WM / 16, TB = GWN / 16;
-  uint32_t aoff[FB], boff[TB];
-#pragma unroll
-  for (int fb = 0; fb < FB; ++fb) aoff[fb] = (uint32_t)(wf + 16 * fb + c16) * 128;
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb) boff[tb] = (uint32_t)(wt + 16 * tb + c16) * 128;
-  const int32_t swz = (c16 >> 1) & 7;  // rows wf + 16 fb + c16 share (row >> 1) & 7
-
-  f32x4 acc[FB][TB];
-#pragma unroll
-  for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[fb][tb] = f32x4{};
-
-  auto frags = [&](const char* a, const char* b, int s, bf16x8 (&af)[FB], bf16x8 (&bf)[TB]) {
-    const uint32_t c = (uint32_t)(((4 * s + lg) ^ swz) << 4);
-#pragma unroll
-    for (int fb = 0; fb < FB; ++fb) af[fb] = *reinterpret_cast<const bf16x8*>(a + aoff[fb] + c);
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) bf[tb] = *reinterpret_cast<const bf16x8*>(b + boff[tb] + c);
-  };
-
-  // The residual epilogue's reads of out[t][f] are issued before the main
-  // loop, so they land during it instead of after it, when every CU of the
-  // launch would read its residual tile at once.  Rows past T read
-  // the last row (valid memory, values unused).
-  constexpr bool PREFETCH = EPI == EPI_RESIDUAL;
-  u32x2 res[PREFETCH ? TB : 1][PREFETCH ? FB : 1];
-  if constexpr (PREFETCH) {
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const int32_t t = min(t0 + wt + 16 * tb + c16, T - 1);
-      const uint16_t* orow = ep.out + (size_t)t * ep.ld_out + f0 + wf + 4 * lg;
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb) res[tb][fb] = *reinterpret_cast<const u32x2*>(orow + 16 * fb);
-    }
-  }
-  // The folded RMSNorm's per-token factors (every epilogue but RESIDUAL):
-  // lane j loads those of the wave's tokens j and j + 64 (two coalesced
-  // loads at most), also before the main loop; the epilogue takes each
-  // token's from its lane.
-  constexpr bool ROWPRE = EPI != EPI_RESIDUAL;
-  constexpr int RT = ROWPRE ? (GWN + 63) / 64 : 1;
+// What an epilogue reads besides the accumulators, loaded before the main loop
+// so that it lands during it.
+// RESIDUAL: the residual stream's out[t][f] (after the loop, every CU of the
+// launch would read its residual tile at once).  Rows past T read the last
+// row (valid memory, values unused).
+// The others: the folded RMSNorm's per-token factors; lane j loads those of
+// the wave's tokens j and j + 64 (two coalesced loads at most), and the
+// epilogue takes each token's from its lane.
+// (RESIDUAL on the widest tiles, above kEarlyResidual blocks of a wave: read in
+// the epilogue, since the registers would spill; out-projection at 18720 tokens
+// on Tile224 90 us, 93 us with the early read.)
+constexpr int kEarlyResidual = 24;
+template <int EPI, int FB, int TB>
+struct EpiPre {
+  static constexpr bool RES = EPI == EPI_RESIDUAL && FB * TB <= kEarlyResidual;
+  static constexpr int RT = EPI == EPI_RESIDUAL ? 1 : (16 * TB + 63) / 64;
+  u32x2 res[RES ? TB : 1][RES ? FB : 1];
   float rtok[RT];
-  if constexpr (ROWPRE) {
-    if (ep.row_scale) {
+  __device__ __forceinline__ void load(const GemmEpilogue& ep, int32_t T, int32_t fw, int32_t tw, int32_t lane) {
+    const int32_t lg = lane >> 4, c16 = lane & 15;
+    if constexpr (RES) {
 #pragma unroll
-      for (int r = 0; r < RT; ++r) rtok[r] = ep.row_scale[min(t0 + wt + 64 * r + lane, T - 1)];
+      for (int tb = 0; tb < TB; ++tb) {
+        const int32_t t = min(tw + 16 * tb + c16, T - 1);
+        const uint16_t* orow = ep.out + (size_t)t * ep.ld_out + fw + 4 * lg;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) res[tb][fb] = *reinterpret_cast<const u32x2*>(orow + 16 * fb);
+      }
+    } else if (EPI != EPI_RESIDUAL && ep.row_scale) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) rtok[r] = ep.row_scale[min(tw + 64 * r + lane, T - 1)];
     }
   }
+};
 
-  const int32_t nk = Kd / GBK;
-  issue(0, 0);
-  landed();
-  for (int32_t kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) issue((kt + 1) * GBK, (kt + 1) & 1);
-    const char* a = smem + (kt & 1) * 2 * G_TILE_BYTES;
-    const char* b = a + G_TILE_BYTES;
-    bf16x8 af[2][FB], bfr[2][TB];
-    frags(a, b, 0, af[0], bfr[0]);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      if (s + 1 < 2) frags(a, b, s + 1, af[(s + 1) & 1], bfr[(s + 1) & 1]);
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb)
-          acc[fb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s & 1][fb], bfr[s & 1][tb],
-                                                                acc[fb][tb], 0, 0, 0);
-    }
-    landed();
-  }
-
-  // epilogue: lane holds D[f][t] for t = t0 + wt + 16 tb + c16 and
-  // f = f0 + wf + 16 fb + 4 lg + e (e = 0..3)
+// The epilogue of a wave's 16 FB features x 16 TB tokens from feature fw and
+// token tw: lane (lg, c16) holds D[f][t] for t = tw + 16 tb + c16 and
+// f = fw + 16 fb + 4 lg + e (e = 0..3) in acc[fb][tb][e].  lds: LDSB bytes
+// that no other wave touches any more.
+template <int EPI, int FB, int TB, int LDSB>
+__device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre<EPI, FB, TB>& pre,
+                                              const GemmEpilogue& ep, int32_t F, int32_t T, int32_t fw,
+                                              int32_t tw, int32_t lane, char* lds) {
+  constexpr int WM = 16 * FB, GWN = 16 * TB;
+  const int32_t lg = lane >> 4, c16 = lane & 15;
   // The folded RMSNorm of the input rows: D is linear in the row, so the
   // token's 1 / rms scales its accumulators before anything else (taken
   // from the lane that loaded it while every lane is active).
-  if constexpr (ROWPRE) {
+  if constexpr (EPI != EPI_RESIDUAL) {
     if (ep.row_scale) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
-        const float r = __shfl(rtok[tb >> 2], 16 * (tb & 3) + c16);
+        const float r = __shfl(pre.rtok[tb >> 2], 16 * (tb & 3) + c16);
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
@@ -256,15 +138,15 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
   if constexpr (EPI == EPI_QKV) {
     // a 256-feature tile lies in one of q, k, v (hidden is a multiple of 256)
     // and each wave's 128 or 64 features in one head (head_dim 128)
-    const int32_t sec = f0 / ep.hidden;
-    const int32_t hf0 = f0 - sec * ep.hidden + wf;       // wave's first feature in its section
+    const int32_t sec = fw / ep.hidden;
+    const int32_t hf0 = fw - sec * ep.hidden;  // wave's first feature in its section
     const int32_t head = hf0 / ep.head_dim;
     const int32_t dbase = hf0 - head * ep.head_dim + 4 * lg;
     if (ep.ss_part && sec < 2) {
       // qk-norm: sums of squares of the raw q or k, then the gain (before
       // RoPE); the 1 / rms factor is applied by norm_scale_kernel
-      store_sum_squares(acc, ep.ss_part, ep.n_part, (f0 + wf) / kSsPartWidth, t0 + wt, T, lg, c16);
-      const float* g = ep.qk_gain + f0 + wf + 4 * lg;
+      store_sum_squares(acc, ep.ss_part, ep.n_part, (fw) / kSsPartWidth, tw, T, lg, c16);
+      const float* g = ep.qk_gain + fw + 4 * lg;
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb) {
         const f32x4 gv = *reinterpret_cast<const f32x4*>(g + 16 * fb);
@@ -282,11 +164,11 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
     // a multiple of 8 tokens (so do nodes), so no run crosses a page.
     if (sec == 2) {
       constexpr int LDSW = GWN + 8;  // staged row length (elements)
-      constexpr int RP = WM * LDSW * 2 * G_NW <= (int)sizeof(smem) ? WM : WM / 2;  // rows per pass
+      constexpr int RP = WM * LDSW * 2 <= LDSB ? WM : WM / 2;  // rows per pass
       constexpr int SEGS = GWN / 8;
-      static_assert(RP * LDSW * 2 * G_NW <= (int)sizeof(smem) && (RP * SEGS) % 64 == 0 && RP % 16 == 0,
+      static_assert(RP * LDSW * 2 <= LDSB && (RP * SEGS) % 64 == 0 && RP % 16 == 0,
                     "v staging layout");
-      uint16_t* lt = reinterpret_cast<uint16_t*>(smem) + (size_t)wave * RP * LDSW;
+      uint16_t* lt = reinterpret_cast<uint16_t*>(lds);
       const int32_t d0 = hf0 - head * ep.head_dim;  // wave's first feature within its head
 #pragma unroll
       for (int pass = 0; pass < WM / RP; ++pass) {
@@ -300,7 +182,7 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
 #pragma unroll
         for (int j = 0; j < RP * SEGS / 64; ++j) {
           const int32_t r = lane + 64 * j, row = r / SEGS, seg = r - row * SEGS;
-          const int32_t t = t0 + wt + 8 * seg;
+          const int32_t t = tw + 8 * seg;
           if (t >= T) continue;
           const u32x4 val = *reinterpret_cast<const u32x4*>(lt + row * LDSW + 8 * seg);
           const int32_t node = (int32_t)fast_div((uint32_t)t, ep.nq_div), tok = t - node * ep.nq;
@@ -342,7 +224,7 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
       }
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-      const int32_t t = t0 + wt + 16 * tb + c16;
+      const int32_t t = tw + 16 * tb + c16;
       if (t >= T) continue;
       const int32_t node = (int32_t)fast_div((uint32_t)t, ep.nq_div), tok = t - node * ep.nq;
       const int32_t frame = (int32_t)fast_div((uint32_t)tok, ep.tpp_div), n = tok - frame * ep.tpp;
@@ -381,22 +263,22 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
     }
   } else {
     if (EPI == EPI_STORE && ep.ss_part)
-      store_sum_squares(acc, ep.ss_part, ep.n_part, (f0 + wf) / kSsPartWidth, t0 + wt, T, lg, c16);
+      store_sum_squares(acc, ep.ss_part, ep.n_part, (fw) / kSsPartWidth, tw, T, lg, c16);
     constexpr int FPG = kSsPartWidth / 16;  // 16-feature blocks per sum-of-squares partial
     static_assert(FB % FPG == 0, "whole partials per wave");
     const bool row_sums = EPI == EPI_RESIDUAL && ep.ss_part;
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-      const int32_t t = t0 + wt + 16 * tb + c16;
+      const int32_t t = tw + 16 * tb + c16;
       if (t >= T) continue;  // uniform over the 4 lanes of a token, so the butterflies below stay inside it
-      uint16_t* orow = ep.out + (size_t)t * ep.ld_out + f0 + wf + 4 * lg;
+      uint16_t* orow = ep.out + (size_t)t * ep.ld_out + fw + 4 * lg;
       float ssq[FB / FPG];
 #pragma unroll
       for (int g = 0; g < FB / FPG; ++g) ssq[g] = 0.f;
       // noise-level gate of this token's node (residual epilogue only)
       const float* gate = nullptr;
       if (EPI == EPI_RESIDUAL && ep.mod)
-        gate = ep.mod + ((size_t)ep.node_level[t / ep.nq] * 6 + ep.gate_row) * F + f0 + wf + 4 * lg;
+        gate = ep.mod + ((size_t)ep.node_level[t / ep.nq] * 6 + ep.gate_row) * F + fw + 4 * lg;
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb) {
           float v[4];
@@ -410,8 +292,8 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
               for (int e = 0; e < 4; ++e) v[e] *= gv[e];
             }
             u32x2 r;
-            if constexpr (PREFETCH)
-              r = res[tb][fb];
+            if constexpr (EpiPre<EPI, FB, TB>::RES)
+              r = pre.res[tb][fb];
             else
               r = *reinterpret_cast<const u32x2*>(dst);
             v[0] += __uint_as_float(r.x << 16);
@@ -438,74 +320,423 @@ __global__ __launch_bounds__(G_THREADS, 1) void gemm_bf16_kernel(const uint16_t*
           float sq = ssq[g];
           sq += __shfl_xor(sq, 16);
           sq += __shfl_xor(sq, 32);
-          if (lg == 0) ep.ss_part[(size_t)((f0 + wf) / kSsPartWidth + g) * T + t] = sq;
+          if (lg == 0) ep.ss_part[(size_t)((fw) / kSsPartWidth + g) * T + t] = sq;
         }
       }
     }
   }
 }
 
-template <int BN, int WL>
-static void launch_gemm_bn(int epi, const uint16_t* W, const uint16_t* X, int32_t F, int32_t T, int32_t Kd,
-                           const GemmEpilogue& ep, hipStream_t stream) {
-  const dim3 grid((uint32_t)(F / GBM) * (uint32_t)((T + BN - 1) / BN));
-  if constexpr (WL == 1) {
-    switch (epi) {
-      case EPI_QKV:
-        hipLaunchKernelGGL((gemm_bf16_kernel<EPI_QKV, BN, 1>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-        break;
-      case EPI_GELU:
-        hipLaunchKernelGGL((gemm_bf16_kernel<EPI_GELU, BN, 1>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-        break;
-      case EPI_RESIDUAL:
-        hipLaunchKernelGGL((gemm_bf16_kernel<EPI_RESIDUAL, BN, 1>), grid, dim3(G_THREADS), 0, stream, W, X, F, T,
-                           Kd, ep);
-        break;
-      default:
-        hipLaunchKernelGGL((gemm_bf16_kernel<EPI_STORE, BN, 1>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-    }
-  } else {
-  switch (epi) {
-    case EPI_QKV:
-      hipLaunchKernelGGL((gemm_bf16_kernel<EPI_QKV, BN, 0>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-      break;
-    case EPI_GELU:
-      hipLaunchKernelGGL((gemm_bf16_kernel<EPI_GELU, BN, 0>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-      break;
-    case EPI_RESIDUAL:
-      hipLaunchKernelGGL((gemm_bf16_kernel<EPI_RESIDUAL, BN, 0>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd,
-                         ep);
-      break;
-    default:
-      hipLaunchKernelGGL((gemm_bf16_kernel<EPI_STORE, BN, 0>), grid, dim3(G_THREADS), 0, stream, W, X, F, T, Kd, ep);
-  }
-  }
+// ------------------------------------------------------ split contractions
+// Partial sums of a split contraction: unit (fu, tu) is 64 features x 16
+// tokens, one wave's f32x4[4][64] block, units of one split feature-major.
+constexpr int UF = 64, UT = 16, UFB = UF / 16;
+__device__ __forceinline__ f32x4* part_unit(const GemmEpilogue& ep, int32_t split, int32_t n_fu, int32_t n_tu,
+                                            int32_t fu, int32_t tu) {
+  return reinterpret_cast<f32x4*>(ep.part) + (((size_t)split * n_fu + fu) * n_tu + tu) * (UFB * 64);
 }
 
-// Tile shape of a launch: one work-group per CU, so a launch of n tiles
-// takes ceil(n / CUs) rounds of one tile's time.  A tile of BN tokens takes
-// BN / 256 of a 256-token tile's time times a per-shape efficiency loss
-// (more fragment reads and copies per MFMA), measured on the Wan block's
-// GEMMs.  The shape with the fewest tile-times wins, the wider one on ties.
-// Layout 1 (224-token tiles, a wave holds 64 features: half a head) serves
-// every epilogue (sums of squares are kept per 64 features).
-struct GemmShape {
-  int bn, wl;
+// Adds a unit's partials in split order and runs the epilogue on the sum: one
+// wave per unit (F T / 1024 of them, so a launch of 128 tokens still has
+// hundreds), four splits' loads in flight at once.  Bound by its launch at
+// small sizes (4 us of 13.6 at 128 tokens x 8960 k in five parts), then by the
+// partials' traffic (9 us for 29 MB).
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, int32_t S, GemmEpilogue ep) {
+  constexpr int LDSB = UF * (UT + 8) * 2;  // the v transpose of the QKV epilogue
+  __shared__ __attribute__((aligned(16))) char smem[EPI == EPI_QKV ? 4 * LDSB : 16];
+  const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t n_fu = F / UF, n_tu = (T + UT - 1) / UT;
+  const int32_t u = blockIdx.x * 4 + wave;
+  if (u >= n_fu * n_tu) return;
+  const int32_t fu = u / n_tu, tu = u - fu * n_tu;
+  EpiPre<EPI, UFB, 1> pre;
+  pre.load(ep, T, fu * UF, tu * UT, lane);
+  f32x4 acc[UFB][1];
+#pragma unroll
+  for (int fb = 0; fb < UFB; ++fb) acc[fb][0] = f32x4{};
+  const f32x4* p = part_unit(ep, 0, n_fu, n_tu, fu, tu) + lane;
+  const size_t stride = (size_t)n_fu * n_tu * (UFB * 64);
+#pragma unroll 4
+  for (int32_t s = 0; s < S; ++s, p += stride)
+#pragma unroll
+    for (int fb = 0; fb < UFB; ++fb) acc[fb][0] += p[fb * 64];
+  gemm_epilogue<EPI, UFB, 1, LDSB>(acc, pre, ep, F, T, fu * UF, tu * UT, lane, smem + wave * LDSB);
+}
+
+// N <= 4 copies of 1 KB each from memory straight into consecutive LDS: lane i
+// of copy j moves 16 bytes from biased + off[j] + 1024 j to lds + 1024 j + 16 i.
+// The instruction's offset field moves the memory and the LDS address alike, so
+// M0, which carries the LDS address, is set once for the group (and restored);
+// off[j] makes up for it (kCopyBias - 1024 j above the lane's own offset, the base kCopyBias
+// lower, so that it stays non-negative; rows come in multiples of 8 and are at
+// least 512 bytes long, so the sum stays below 2^32 for operands of up to 4 GB).
+// Written as inline asm: while a copy
+// it knows of is in flight, the compiler waits for every LDS fragment read with
+// lgkmcnt(0); not knowing of these, it counts the reads exactly.  The copies
+// complete under the ring's explicit vmcnt waits.
+constexpr uint32_t kCopyBias = 3072;
+template <int N>
+__device__ __forceinline__ void copy_group(const char* biased, const uint32_t* off, char* lds) {
+  const uint32_t l = (uint32_t)reinterpret_cast<uintptr_t>(lds);
+  uint32_t saved;
+  static_assert(N >= 1 && N <= 4, "copies per group");
+  if constexpr (N == 1)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %3, %1\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(biased), "s"(l), "v"(off[0])
+        : "memory");
+  else if constexpr (N == 2)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %3, %1\n\t"
+        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1])
+        : "memory");
+  else if constexpr (N == 3)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %3, %1\n\t"
+        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
+        "global_load_lds_dwordx4 %5, %1 offset:2048\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1]), "v"(off[2])
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %3, %1\n\t"
+        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
+        "global_load_lds_dwordx4 %5, %1 offset:2048\n\t"
+        "global_load_lds_dwordx4 %6, %1 offset:3072\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3])
+        : "memory");
+}
+
+// Stage wait of the ring: all but this wave's N newest copies have landed and
+// its own fragment reads are done; then the same of every wave.
+template <int N>
+__device__ __forceinline__ void ring_wait() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// A tile shape: BM features x BN tokens per work-group, WF x WT waves of
+// BM / WF x BN / WT, KW groups of them that take the two 32-k halves of each
+// 64-k stage (KW = 2) or both (KW = 1), D stages in the LDS ring, WPE waves
+// per SIMD.
+template <int BM_, int BN_, int WF_, int WT_, int KW_, int D_, int WPE_>
+struct GemmTile {
+  static constexpr int BM = BM_, BN = BN_, WF = WF_, WT = WT_, KW = KW_, D = D_, WPE = WPE_;
 };
-static GemmShape gemm_tile_shape(int32_t F, int32_t T) {
-  GemmShape best{256, 0};
+
+template <int EPI, class C>
+__global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_kernel(
+    const uint16_t* __restrict__ W, const uint16_t* __restrict__ X, int32_t F, int32_t T, int32_t Kd, int32_t S,
+    GemmEpilogue ep) {
+  constexpr int BM = C::BM, BN = C::BN, WF = C::WF, WT = C::WT, KW = C::KW, D = C::D;
+  constexpr int NW = WF * WT * KW, WM = BM / WF, GWN = BN / WT, FB = WM / 16, TB = GWN / 16, TBO = TB / KW;
+  constexpr int STAGE = (BM + BN) * GBK * 2, XO = BM * GBK * 2;
+  constexpr int NQ = 2 / KW;  // 32-k steps of a wave per stage
+  // copies: a wave moves NCW groups of 8 weight rows and NCX of 8 token rows
+  // per stage, the last waves one fewer where the groups do not divide evenly
+  constexpr int NCW = BM / 8 / NW, XG = BN / 8, NCX = (XG + NW - 1) / NW, XFULL = XG - (NCX - 1) * NW, NC = NCW + NCX;
+  static_assert(NCW * NW * 8 == BM && NCW <= 4 && NCX <= 4 && D >= 2 && D <= 5 && (D - 1) * NC <= 63, "copy split");
+  static_assert(XFULL == NW || D == 2, "uneven copies need full waits");
+  static_assert((KW == 1 || KW == 2) && TBO * KW == TB && FB % UFB == 0 && GWN % 16 == 0, "wave split");
+  static_assert((KW - 1) * BM * BN * 4 <= D * STAGE, "the exchange fits the ring");
+  // stage s: weight rows at s * STAGE, token rows XO further; rows of 64 k
+  // (128 B) with 16-byte column c stored at c ^ ((row >> 1) & 7)
+  __shared__ __attribute__((aligned(1024))) char smem[D * STAGE];
+  const int32_t n_tf = F / BM, n_tt = (T + BN - 1) / BN, n_tiles = n_tf * n_tt;
+  // Each XCD takes a contiguous run of logical items (all tiles of one part of
+  // the contraction, then the next part); the tiles are walked in groups of GT
+  // token tiles, feature tiles outermost within a group, so that the tiles an
+  // XCD holds at once share a few weight and 8 token panels in its L2.
+  constexpr int32_t GT = 8;
+  const int32_t item = (int32_t)xcd_remap(blockIdx.x, (uint32_t)(n_tiles * S));
+  const int32_t split = item / n_tiles, tile = item - split * n_tiles;
+  const int32_t group = tile / (GT * n_tf), in_group = tile - group * GT * n_tf;
+  const int32_t gt = min(GT, n_tt - group * GT);
+  const int32_t tf = in_group / gt, tt = group * GT + in_group % gt;
+  const int32_t f0 = tf * BM, t0 = tt * BN;
+  const int32_t tid = threadIdx.x, lane = tid & 63;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS copy addresses stay scalar
+  const int32_t lg = lane >> 4, c16 = lane & 15;
+  const int32_t kw = wave / (WF * WT), wid = wave % (WF * WT);
+  const int32_t wf = (wid % WF) * WM, wt = (wid / WF) * GWN;
+  const int32_t nk = Kd / GBK, kt0 = (int32_t)((int64_t)split * nk / S);
+  const int32_t n = (int32_t)((int64_t)(split + 1) * nk / S) - kt0;  // stages of this part
+
+  uint32_t woff[NCW], xoff[NCX];
+  const int32_t wg0 = NCW * wave, xg0 = NCX * wave - max(0, wave - XFULL);  // first row groups of this wave
+#pragma unroll
+  for (int j = 0; j < NCW; ++j) {
+    const int32_t row = 8 * (wg0 + j) + (lane >> 3);
+    woff[j] = ((uint32_t)(f0 + row) * Kd + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2 + kCopyBias - 1024 * j;
+  }
+#pragma unroll
+  for (int j = 0; j < NCX; ++j) {
+    const int32_t row = 8 * (xg0 + j) + (lane >> 3);
+    xoff[j] = ((uint32_t)min(t0 + row, T - 1) * Kd + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2 + kCopyBias - 1024 * j;
+  }
+  const char* wk = reinterpret_cast<const char*>(W) + (size_t)kt0 * GBK * 2 - kCopyBias;
+  const char* xk = reinterpret_cast<const char*>(X) + (size_t)kt0 * GBK * 2 - kCopyBias;
+  int32_t in_slot = 0;
+  auto issue = [&]() __attribute__((always_inline)) {  // the next stage into the next slot
+    char* st = smem + in_slot;
+    copy_group<NCW>(wk, woff, st + wg0 * 1024);
+    if (XFULL == NW || wave < XFULL)
+      copy_group<NCX>(xk, xoff, st + XO + xg0 * 1024);
+    else if constexpr (NCX > 1)
+      copy_group<NCX - 1>(xk, xoff, st + XO + xg0 * 1024);
+    wk += GBK * 2;
+    xk += GBK * 2;
+    in_slot = in_slot + STAGE == D * STAGE ? 0 : in_slot + STAGE;
+  };
+  const int32_t tw = t0 + wt + 16 * TBO * kw;  // first token of the blocks this wave finishes
+  EpiPre<EPI, FB, TBO> pre;
+  if (S == 1) pre.load(ep, T, f0 + wf, tw, lane);
+#pragma unroll
+  for (int j = 0; j < D - 1; ++j)
+    if (j < n) issue();
+
+  // 16x16x32 MFMAs: lane (lg, c16) supplies row c16 of each 16-row operand
+  // block with k values 8 lg .. 8 lg + 7 of a 32-k step
+  f32x4 acc[FB][TB];
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) acc[fb][tb] = f32x4{};
+  const int32_t swz = (c16 >> 1) & 7;  // rows wf + 16 fb + c16 share (row >> 1) & 7
+  const uint32_t arow = (uint32_t)(wf + c16) * 128, brow = XO + (uint32_t)(wt + c16) * 128;
+  uint32_t col[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) col[q] = (uint32_t)(((4 * (KW == 2 ? kw : q) + lg) ^ swz) << 4);
+  bf16x8 af[2][FB], bfr[2][TB];
+  int32_t slot = 0;
+  auto read = [&](int b, int q) __attribute__((always_inline)) {
+    const char* st = smem + slot;
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb) af[b][fb] = *reinterpret_cast<const bf16x8*>(st + arow + col[q] + fb * 2048);
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) bfr[b][tb] = *reinterpret_cast<const bf16x8*>(st + brow + col[q] + tb * 2048);
+  };
+  auto advance = [&]() __attribute__((always_inline)) { slot = slot + STAGE == D * STAGE ? 0 : slot + STAGE; };
+  auto mul = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+        acc[fb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[b][fb], bfr[b][tb], acc[fb][tb], 0, 0, 0);
+  };
+  // all but the newest stages have landed, `newer` of them issued after the awaited one
+  auto wait = [&](int32_t newer) __attribute__((always_inline)) {
+    if (newer >= D - 2)
+      ring_wait<(D - 2) * NC>();
+    else if (D > 4 && newer == 2)
+      ring_wait<2 * NC>();
+    else if (D > 3 && newer == 1)
+      ring_wait<NC>();
+    else
+      ring_wait<0>();
+  };
+  // Fragments are read one 32-k step ahead of their MFMAs, across the stage
+  // boundary too, so that neither the barrier nor a read's latency stands
+  // between two steps.  A stage's slot is free at the barrier after its last
+  // reads, where the stage D later is issued into it.
+  wait(n - 1);
+  read(0, 0);
+  if constexpr (NQ == 2) {
+    if (D - 1 < n) issue();
+    for (int32_t i = 0; i + 1 < n; ++i) {
+      read(1, 1);
+      mul(0);
+      advance();
+      wait(n - 2 - i);
+      if (i + D < n) issue();
+      read(0, 0);
+      mul(1);
+    }
+    read(1, 1);
+    mul(0);
+    mul(1);
+  } else {
+    if (D - 1 < n) issue();
+    int32_t i = 0;
+    for (; i + 2 < n; i += 2) {
+      advance();
+      wait(n - 2 - i);
+      if (i + D < n) issue();
+      read(1, 0);
+      mul(0);
+      advance();
+      wait(n - 3 - i);
+      if (i + 1 + D < n) issue();
+      read(0, 0);
+      mul(1);
+    }
+    if (i + 2 == n) {
+      advance();
+      wait(0);
+      read(1, 0);
+      mul(0);
+      mul(1);
+    } else {
+      mul(0);
+    }
+  }
+  // the k groups' sums of each wave tile, added in group order by the group
+  // that finishes the block
+  f32x4 sum[FB][TBO];
+  constexpr int OWN = FB * TBO;  // blocks a wave finishes
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int tb = 0; tb < TBO; ++tb) sum[fb][tb] = acc[fb][tb];
+  } else {
+    ring_wait<0>();  // every wave is done with the ring
+    f32x4* const red = reinterpret_cast<f32x4*>(smem);
+    f32x4* p = red + (size_t)((1 - kw) * WF * WT + wid) * OWN * 64 + lane;
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int tb = 0; tb < TBO; ++tb) p[(fb * TBO + tb) * 64] = kw ? acc[fb][tb] : acc[fb][TBO + tb];
+    __syncthreads();
+    p = red + (size_t)wave * OWN * 64 + lane;
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int tb = 0; tb < TBO; ++tb)
+        sum[fb][tb] = (kw ? acc[fb][TBO + tb] : acc[fb][tb]) + p[(fb * TBO + tb) * 64];
+  }
+  if (S > 1) {
+    const int32_t n_fu = F / UF, n_tu = (T + UT - 1) / UT;
+#pragma unroll
+    for (int g = 0; g < FB / UFB; ++g)
+#pragma unroll
+      for (int tb = 0; tb < TBO; ++tb) {
+        const int32_t tu = tw / UT + tb;
+        if (tu >= n_tu) continue;
+        f32x4* p = part_unit(ep, split, n_fu, n_tu, (f0 + wf) / UF + g, tu) + lane;
+#pragma unroll
+        for (int fb = 0; fb < UFB; ++fb) p[fb * 64] = sum[g * UFB + fb][tb];
+      }
+    return;
+  }
+  constexpr int LDSB = KW == 1 ? D * STAGE / NW : OWN * 1024;
+  if (KW == 1 && EPI == EPI_QKV) __syncthreads();  // every wave is done with the ring: v is staged in it
+  gemm_epilogue<EPI, FB, TBO, LDSB>(sum, pre, ep, F, T, f0 + wf, tw, lane, smem + wave * LDSB);
+}
+
+// The tile shapes: wide ones where the tiles fill the chip, narrow ones (the
+// last four) where wide tiles would leave CUs idle.
+using Tile256 = GemmTile<256, 256, 2, 4, 1, 2, 2>;
+using Tile224 = GemmTile<256, 224, 4, 2, 1, 2, 2>;
+using Tile192 = GemmTile<256, 192, 4, 2, 1, 2, 2>;
+using Tile256x128 = GemmTile<256, 128, 4, 2, 1, 3, 2>;
+using Tile128 = GemmTile<128, 128, 2, 4, 1, 2, 4>;      // two work-groups per CU
+using Tile128Deep = GemmTile<128, 128, 2, 2, 2, 4, 2>;  // one per CU, a deeper ring
+using Tile64 = GemmTile<64, 64, 1, 2, 2, 5, 2>;         // two per CU
+
+// What a launch costs, in us, measured on the four projections of the
+// 1536 / 8960-wide block over 64 .. 23400 tokens with every tile and split
+// forced: a CU's work-groups take `stage` per 64 k and `fixed` for the rest
+// (first copies, epilogue), a lone one on a CU that could hold two
+// `stage1`, `fixed1`; `once` is paid once per launch.
+struct TileCost {
+  int bm, bn, slots;  // work-groups resident at once
+  double stage, fixed, stage1, fixed1, once;
+};
+constexpr TileCost kTiles[] = {
+    {256, 256, kCUs, 1.43, 10.2, 1.43, 10.2, 0.0},     {256, 224, kCUs, 1.34, 9.0, 1.34, 9.0, 0.0},
+    {256, 192, kCUs, 1.11, 9.3, 1.11, 9.3, 0.0},       {256, 128, kCUs, 0.81, 6.2, 0.81, 6.2, 0.0},
+    {128, 128, 2 * kCUs, 0.85, 5.7, 0.73, 4.0, 0.0},   {128, 128, kCUs, 0.46, 4.5, 0.46, 4.5, 0.0},
+    {64, 64, kCUs, 0.184, 0.6, 0.184, 0.6, 3.5},
+};
+constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
+// Tile256's 128 x 64 wave tiles spill with these epilogues' state (104 and 96
+// registers; QKV 18720 tokens 331 us against 272 on Tile224): not built.
+constexpr bool tile256_built(int epi) { return epi == EPI_GELU || epi == EPI_STORE; }
+
+// The tile and the number of parts of the contraction of a launch: the
+// cheapest by the table.  A launch of n work-groups takes ceil(n / slots)
+// rounds, and split S ways it adds the reduce launch and its traffic (3.5 us
+// and 0.2 us per MB of partials), which pays where the tiles alone leave most
+// CUs idle: 1536 features x 8960 k at 128 tokens 30.6 us on 48 64 x 64 tiles,
+// 13.6 us in five parts (125 us on the 256 x 128 tiles that were the only choice).
+struct GemmShape {
+  int tile, split;
+};
+constexpr int kGemmMaxSplit = 16;
+static GemmShape gemm_shape(int epi, int32_t F, int32_t T, int32_t Kd, size_t part_bytes) {
+  const int32_t nk = Kd / GBK;
+  GemmShape best{1, 1};
   double best_cost = 1e30;
-  const GemmShape cands[] = {{256, 0}, {224, 1}, {192, 0}, {128, 0}};
-  for (const GemmShape c : cands) {
-    const int64_t tiles = (int64_t)(F / GBM) * ((T + c.bn - 1) / c.bn);
-    const double eff = c.bn == 256 ? 1.0 : c.bn == 224 ? 1.02 : c.bn == 192 ? 1.12 : 1.4;
-    const double cost = (double)((tiles + kCUs - 1) / kCUs) * c.bn / 256.0 * eff;
-    if (cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = c;
+  for (int i = tile256_built(epi) ? 0 : 1; i < kTileCount; ++i) {
+    const TileCost& c = kTiles[i];
+    const int64_t tiles = (int64_t)(F / c.bm) * ((T + c.bn - 1) / c.bn);
+    for (int32_t S = 1; S <= kGemmMaxSplit && S <= nk; ++S) {
+      const double bytes = S > 1 ? 4.0 * S * F * ((T + UT - 1) / UT * UT) : 0.0;
+      if (bytes > (double)part_bytes) break;
+      const int64_t full = tiles * S / c.slots, rest = tiles * S % c.slots;
+      const double n = (double)((nk + S - 1) / S);
+      double cost = c.once + (double)full * (n * c.stage + c.fixed) + (S > 1 ? 3.5 + 0.2e-6 * bytes : 0.0);
+      if (rest) cost += rest <= kCUs ? n * c.stage1 + c.fixed1 : n * c.stage + c.fixed;
+      // the QKV epilogue (RoPE, page scatter), exposed where no other
+      // work-group of the CU covers it: 2.5 - 4 us per round
+      if (epi == EPI_QKV && c.slots == kCUs) cost += 3.0 * (double)(full + (rest != 0));
+      if (cost < best_cost - 1e-9) {
+        best_cost = cost;
+        best = GemmShape{i, S};
+      }
     }
   }
   return best;
+}
+
+template <int EPI, class C>
+static void launch_tile(const uint16_t* W, const uint16_t* X, int32_t F, int32_t T, int32_t Kd, int32_t S,
+                        const GemmEpilogue& ep, hipStream_t stream) {
+  const dim3 grid((uint32_t)(F / C::BM) * (uint32_t)((T + C::BN - 1) / C::BN) * (uint32_t)S);
+  hipLaunchKernelGGL((gemm_bf16_kernel<EPI, C>), grid, dim3(64 * C::WF * C::WT * C::KW), 0, stream, W, X, F, T, Kd, S,
+                     ep);
+}
+
+template <int EPI>
+static void launch_epi(GemmShape g, const uint16_t* W, const uint16_t* X, int32_t F, int32_t T, int32_t Kd,
+                       const GemmEpilogue& ep, hipStream_t stream) {
+  switch (g.tile) {
+    case 0:
+      if constexpr (tile256_built(EPI)) launch_tile<EPI, Tile256>(W, X, F, T, Kd, g.split, ep, stream);
+      break;
+    case 1: launch_tile<EPI, Tile224>(W, X, F, T, Kd, g.split, ep, stream); break;
+    case 2: launch_tile<EPI, Tile192>(W, X, F, T, Kd, g.split, ep, stream); break;
+    case 3: launch_tile<EPI, Tile256x128>(W, X, F, T, Kd, g.split, ep, stream); break;
+    case 4: launch_tile<EPI, Tile128>(W, X, F, T, Kd, g.split, ep, stream); break;
+    case 5: launch_tile<EPI, Tile128Deep>(W, X, F, T, Kd, g.split, ep, stream); break;
+    default: launch_tile<EPI, Tile64>(W, X, F, T, Kd, g.split, ep, stream);
+  }
+  if (g.split > 1) {
+    const uint32_t units = (uint32_t)(F / UF) * (uint32_t)((T + UT - 1) / UT);
+    hipLaunchKernelGGL((gemm_reduce_kernel<EPI>), dim3((units + 3) / 4), dim3(256), 0, stream, F, T, g.split, ep);
+  }
 }
 
 int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, int32_t F, int32_t T,
@@ -515,8 +746,8 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
                 F, Kd, T);
   if ((uint64_t)F * Kd * 2 > 0xffffffffull || (uint64_t)T * Kd * 2 > 0xffffffffull)
     return fail(SC_EUNSUPPORTED, "gemm operands beyond 4 GB");
-  if (epi == EPI_QKV && (ep.hidden % GBM || ep.head_dim != GWM))
-    return fail(SC_EUNSUPPORTED, "QKV epilogue needs hidden %% %d == 0 and head_dim %d", GBM, GWM);
+  if (epi == EPI_QKV && (ep.hidden % GBM || ep.head_dim != 128))
+    return fail(SC_EUNSUPPORTED, "QKV epilogue needs hidden %% %d == 0 and head_dim 128", GBM);
   if (ep.row_scale && epi == EPI_RESIDUAL) return fail(SC_EINVAL, "row_scale is not a RESIDUAL epilogue input");
   GemmEpilogue e = ep;
   if (epi == EPI_QKV) {
@@ -530,15 +761,13 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
     e.gw_div = magic_div((uint32_t)ep.grid_w);
   }
   timer_begin(timer_kind, stream);
-  const GemmShape shape = gemm_tile_shape(F, T);
-  if (shape.wl == 1)
-    launch_gemm_bn<224, 1>(epi, W, X, F, T, Kd, e, stream);
-  else if (shape.bn == 128)
-    launch_gemm_bn<128, 0>(epi, W, X, F, T, Kd, e, stream);
-  else if (shape.bn == 192)
-    launch_gemm_bn<192, 0>(epi, W, X, F, T, Kd, e, stream);
-  else
-    launch_gemm_bn<256, 0>(epi, W, X, F, T, Kd, e, stream);
+  const GemmShape g = gemm_shape(epi, F, T, Kd, ep.part ? ep.part_bytes : 0);
+  switch (epi) {
+    case EPI_QKV: launch_epi<EPI_QKV>(g, W, X, F, T, Kd, e, stream); break;
+    case EPI_GELU: launch_epi<EPI_GELU>(g, W, X, F, T, Kd, e, stream); break;
+    case EPI_RESIDUAL: launch_epi<EPI_RESIDUAL>(g, W, X, F, T, Kd, e, stream); break;
+    default: launch_epi<EPI_STORE>(g, W, X, F, T, Kd, e, stream);
+  }
   timer_end(timer_kind, stream);
   SC_HIP(hipGetLastError());
   return SC_OK;
