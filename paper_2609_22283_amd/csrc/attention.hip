@@ -13,6 +13,9 @@
 // softmax in fp32.  The K rows feeding the S^T MFMA are permuted so that each
 // lane's probabilities are exactly the B operand of the PV MFMA, and V is
 // stored transposed in the cache so its A operand is one 16-byte LDS read.
+// Two narrower forms of it and one that splits a node's keys over the waves of
+// a work-group (attn_waves_kernel) serve shorter nodes and contexts;
+// attn_schedule chooses.
 #include <algorithm>
 #include <climits>
 #include <cstring>
@@ -1049,6 +1052,199 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || D == 4 ? 1 : 2) void attn_bf16_
   for (int qb = 0; qb < 2; ++qb) store_rows<BQ>(it, g, o, oacc[qb], m[qb], l[qb], wave * 32 + 16 * qb + c, lg);
 }
 
+// ------------------------------------------------ bf16 kernel, keys over waves
+// For launches whose 64 .. 256-query units would leave most CUs idle.  A
+// work-group takes 32 queries of one (node, head); its eight waves take eight
+// contiguous parts of the node's 32-key tiles, each through an LDS region of its
+// own with an online softmax of its own, and merge through LDS at the end, in
+// wave order: no barrier in the loop, no partials in memory, no combine launch.
+// K(t + 1) is copied over K(t) once S(t) has read it and V(t + 1) over V(t)
+// likewise, so about a tile is in flight per wave, 64 - 128 KB per CU.
+// What bounds it: the copies (128 KB per CU and step of 256 keys, 1.7 us) and a
+// fixed 7 us of launch, first tile and merge.  One node of 64 queries over 1344
+// keys, 12 heads: 17 us (43 on one 64-query unit per head); 4 x 128 over 896:
+// 15 us (21); 128 over 512: 10.5 us (14.7).  The same with the operands loaded
+// to registers took 25 us for the first: adjacent lanes hold adjacent rows, so
+// each 16-byte load is a cache access of its own.
+constexpr int WV_NW = 8, WV_BQ = 32, WV_BK = 32;
+constexpr int WV_RED = 8 * WV_NW * 2 * 64 * 16;  // merge: [16-channel block][wave][query block][lane] f32x4
+static_assert(WV_NW * (Tile<1>::KT_BYTES + Tile<1>::VT_BYTES) <= WV_RED, "the waves' tiles fit the merge buffer");
+
+// A tile of one wave's own: the copies of KvTiles<1, 1>, four to an M0 setting.
+// (The biased offsets stay below 2^32: a group's first rows lie at least
+// kCopyBias bytes before the end of the slot.)
+struct WaveTiles : KvTiles<1, 1> {
+  using Base = KvTiles<1, 1>;
+  const char* biased;
+  __device__ __forceinline__ WaveTiles(const AttnPlan& plan, const AttnGeom& g, int32_t node, int32_t head,
+                                       int32_t lane)
+      : Base(plan, g, node, head, 0, lane), biased(lbase - kCopyBias) {}
+  __device__ __forceinline__ void copy_k(int32_t t0, uint32_t lds, const Slots& sl) const {
+    const int32_t bkey = (sl.plo + 1) * tpp;
+    const uint32_t lo = sl.lo + khead + (uint32_t)(t0 - sl.plo * tpp) * 256;
+    const uint32_t hi = sl.hi + khead + (uint32_t)(t0 - bkey) * 256;
+    const int32_t lim = nk - t0, split = bkey - t0;
+#pragma unroll
+    for (int h = 0; h < KCP / 4; ++h) {
+      uint32_t off[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int32_t rg = 16 * h + 4 * j;
+        off[j] = (rg >= lim ? kbad + (klane[4 * h + j] & 255u) : (rg >= split ? hi : lo) + klane[4 * h + j]) +
+                 (kCopyBias - 1024 * j);
+      }
+      copy_group<4>(biased, off, lds + 4096 * h);
+    }
+  }
+  __device__ __forceinline__ void copy_v(int32_t t0, uint32_t lds, const Slots& sl) const {
+    const int32_t bkey = (sl.plo + 1) * tpp;
+    const uint32_t lo = sl.lo + vhead + (uint32_t)(t0 - sl.plo * tpp) * 2;
+    const uint32_t hi = sl.hi + vhead + (uint32_t)(t0 - bkey) * 2;
+    const int32_t lim = nk - t0, split = bkey - t0;
+#pragma unroll
+    for (int h = 0; h < VCP / 4; ++h) {
+      uint32_t off[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int32_t rk = vkey[4 * h + j];
+        const bool in = rk < lim;
+        off[j] = (in && rk >= split ? hi : lo) + vlane[4 * h + j] - (in ? 0u : (uint32_t)rk * 2) + (kCopyBias - 1024 * j);
+      }
+      copy_group<4>(biased, off, lds + 4096 * h);
+    }
+  }
+};
+
+// All but this wave's N newest copies have landed.
+template <int N>
+__device__ __forceinline__ void copies_landed() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// This wave's LDS reads are done: what they read may be copied over.
+__device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+__global__ __launch_bounds__(64 * WV_NW, 2) void attn_waves_kernel(const uint16_t* __restrict__ q,
+                                                                   uint16_t* __restrict__ o, AttnGeom g,
+                                                                   AttnPlan plan) {
+  __shared__ __attribute__((aligned(1024))) char smem[WV_RED];
+  __shared__ float ml[2][WV_NW][WV_BQ];
+  using KV = WaveTiles;
+  constexpr int KC = KV::KCP, VC = KV::VCP;  // copies of a K and of a V^T tile
+  const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t lg = lane >> 4, c = lane & 15;
+  // query tiles fastest: an XCD's work-groups share the K/V of a few (node, head)s
+  const int32_t unit = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
+  const int32_t qt = unit % g.n_qtiles, nh = unit / g.n_qtiles;
+  const int32_t node = nh % g.n_nodes, head = nh / g.n_nodes;
+  const KV kv(plan, g, node, head, lane);
+  const int32_t nt = (kv.nk + WV_BK - 1) / WV_BK;
+  const int32_t t_end = (wave + 1) * nt / WV_NW;
+  int32_t t = wave * nt / WV_NW;
+  char* const kl = smem + wave * (Tile<1>::KT_BYTES + Tile<1>::VT_BYTES);
+  char* const vl = kl + Tile<1>::KT_BYTES;
+  const uint32_t kd = __builtin_amdgcn_readfirstlane(lds_addr(kl)), vd = kd + Tile<1>::KT_BYTES;  // for the copies
+  const AttnLane L = attn_lane<1>(c, lg);
+  bf16x8 qreg[2][4];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) load_q(q, g, node, head, qt * WV_BQ + 16 * qb + c, lg, qreg[qb]);
+  if (t < t_end) {
+    const KV::Slots sl = kv.slots(t * WV_BK);
+    kv.copy_k(t * WV_BK, kd, sl);
+    kv.copy_v(t * WV_BK, vd, sl);
+  }
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) scale_q(g, qreg[qb]);
+  f32x4 oacc[2][8], lsum[2] = {f32x4{}, f32x4{}};
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < 8; ++db) oacc[qb][db] = f32x4{};
+  // m: the maximum logit so far (log2 units), the base of the exponents; lim:
+  // what a tile's maximum above m has to exceed to raise it (-inf before the
+  // first finite one)
+  float m[2] = {0.f, 0.f}, lim[2] = {-INFINITY, -INFINITY};
+  const bf16x8 ones = ones_row(c);
+  while (t < t_end) {
+    const int32_t t0 = t * WV_BK, tn = t0 + WV_BK;
+    const bool more = t + 1 < t_end;
+    const KV::Slots sl = kv.slots(min(tn, kv.nk - 1));
+    copies_landed<VC>();  // K(t); V(t) may still be under way
+    STile<1> s;
+    qk_tile<1>(kl, L, qreg, s, m);
+    reads_done();
+    if (more) kv.copy_k(tn, kd, sl);
+    if (kv.nk < tn) mask_tile<1>(s, t0, kv.nk, lg);
+    float mx[2];
+    tile_max<1>(s, mx);
+    if (__builtin_amdgcn_ballot_w64(mx[0] > lim[0] || mx[1] > lim[1])) {
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        const bool up = mx[qb] > lim[qb];
+        const float d = up ? mx[qb] : 0.f;
+        const float alpha = lim[qb] == 0.f ? __builtin_amdgcn_exp2f(-d) : 1.f;  // nothing to scale before the first
+        m[qb] += d;
+        lim[qb] = up ? 0.f : lim[qb];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[0][b][qb][r] -= d;
+        lsum[qb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) oacc[qb][db] *= alpha;
+      }
+    }
+    bf16x8 pb[1][2];
+    probs<1>(s, pb);
+    if (more)
+      copies_landed<KC>();  // V(t); K(t + 1) may still be under way
+    else
+      copies_landed<0>();
+    pv_tile<1>(vl, L, pb, oacc);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) lsum[qb] = mfma16(ones, pb[0][qb], lsum[qb]);
+    reads_done();
+    if (more) kv.copy_v(tn, vd, sl);
+    ++t;
+  }
+  // merge: a wave without a finite logit adds zeros (weight 2^-inf)
+  if (lg == 0)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      ml[0][wave][16 * qb + c] = lim[qb] == 0.f ? m[qb] : -INFINITY;
+      ml[1][wave][16 * qb + c] = lsum[qb][0];
+    }
+  __syncthreads();  // every wave is done with its tiles
+  f32x4* const red = reinterpret_cast<f32x4*>(smem);
+  float inv[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    float mt = -INFINITY, lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < WV_NW; ++w) mt = fmaxf(mt, ml[0][w][16 * qb + c]);
+#pragma unroll
+    for (int w = 0; w < WV_NW; ++w) lt += ml[1][w][16 * qb + c] * __builtin_amdgcn_exp2f(ml[0][w][16 * qb + c] - mt);
+    inv[qb] = 1.f / lt;
+    const float f = __builtin_amdgcn_exp2f(ml[0][wave][16 * qb + c] - mt);
+#pragma unroll
+    for (int db = 0; db < 8; ++db) red[((db * WV_NW + wave) * 2 + qb) * 64 + lane] = oacc[qb][db] * f;
+  }
+  __syncthreads();
+  // wave w finishes channels 16 w .. 16 w + 15
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    f32x4 a = red[(wave * WV_NW * 2 + qb) * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < WV_NW; ++w) a += red[((wave * WV_NW + w) * 2 + qb) * 64 + lane];
+    const int32_t row = qt * WV_BQ + 16 * qb + c;
+    if (row < g.nq) {
+      u32x2 v;
+      v.x = pack_bf16x2(a[0] * inv[qb], a[1] * inv[qb]);
+      v.y = pack_bf16x2(a[2] * inv[qb], a[3] * inv[qb]);
+      *reinterpret_cast<u32x2*>(o + (((size_t)node * g.nq + row) * g.n_heads + head) * HDB + 16 * wave + 4 * lg) = v;
+    }
+  }
+}
+
 // Merges the pieces of each tail unit, in piece order.  A work-group takes 8
 // query rows of one tail unit; 32 lanes share a row, each holding 4 of its
 // 128 outputs, so every partial row is read as one contiguous 512-byte run.
@@ -1088,20 +1284,13 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(uint16_t* __restrict_
   *reinterpret_cast<u32x2*>(o + (((size_t)node * g.nq + qrow) * g.n_heads + head) * HDB + 4 * dl) = r;
 }
 
-// Tail split for a plan: units = heads x nodes x query tiles; the last
-// (units mod resident work-groups) are cut into S pieces, S chosen to
-// minimise the tail's rounds (in units of one whole unit) plus a per-piece
-// cost of about two key tiles (prologue and partial write), with at most
-// max_pieces pieces and no more pieces than the shortest node has key
-// tiles.
-// The kernel form for a plan: queries per work-group (the smallest of 64,
-// 128, 256 that holds a node), 32-key halves per key tile and ring depth.
-// Nodes of at most 64 queries take the streaming form (ring 4 when the units
-// fit the 512 work-groups resident with it, else ring 3 with 768); larger
-// ones the long-context form.  (The streaming form with 128 queries per
-// work-group measured 2-8 % slower than the long-context one on the
-// short-context sweep: its 32-key steps cost more than the deeper ring
-// gains.)
+// A form of the unit kernel: queries per work-group, 32-key halves per key tile
+// and ring depth; attn_shape gives the widest form that a plan's nodes fill (64,
+// 128 or 256 queries).  Nodes of at most 64 queries take the streaming form
+// (ring 4 when the units fit the 512 work-groups resident with it, else ring 3
+// with 768); larger ones a long-context form.  (The streaming form with 128
+// queries per work-group measured 2-8 % slower than the long-context one on the
+// short-context sweep: its 32-key steps cost more than the deeper ring gains.)
 struct AttnShape {
   int32_t bq, kh, ring;
 };
@@ -1125,13 +1314,24 @@ static AttnShape attn_shape(const sc_plan* p, const sc_cache* c) {
   return s;
 }
 
-struct TailSplit {
+// A schedule: the form, its whole units, and its tail units with their pieces each.
+struct AttnSchedule {
   AttnShape sh;
   int32_t whole, tail, split;
+  size_t partial_bytes() const {
+    return split == 1 ? 0 : (size_t)tail * split * sh.bq * (HDB + 2) * sizeof(float);
+  }
 };
-static TailSplit tail_split(const sc_plan* p, const sc_cache* c, int32_t max_pieces = kAttnMaxPieces) {
+
+// The workspace of a plan is the room for the partials of this schedule, on the
+// widest form: units = heads x nodes x query tiles; the last (units mod resident
+// work-groups) are cut into S pieces, S chosen to minimise the tail's rounds (in
+// units of one whole unit) plus a per-piece cost of about two key tiles, with
+// at most kAttnMaxPieces pieces and no more pieces than the shortest node has
+// key tiles.  attn_schedule picks what runs within that room.
+static AttnSchedule workspace_schedule(const sc_plan* p, const sc_cache* c) {
   const int32_t n = (int32_t)p->nodes.size();
-  TailSplit ts;
+  AttnSchedule ts;
   ts.sh = attn_shape(p, c);
   const int32_t bq = ts.sh.bq, bk = 32 * ts.sh.kh;
   const int32_t n_qtiles = (p->nq + bq - 1) / bq;
@@ -1154,7 +1354,7 @@ static TailSplit tail_split(const sc_plan* p, const sc_cache* c, int32_t max_pie
   // K/V streaming sweep).  The threshold is in 64-key tiles.
   if (ts.tail == 0 || mean_tiles * bk < kAttnMinSplitTiles * 64) return ts;
   double best = 1e30;
-  const int32_t smax = std::max(1, std::min({16, max_pieces / ts.tail, min_tiles}));
+  const int32_t smax = std::max(1, std::min({16, kAttnMaxPieces / ts.tail, min_tiles}));
   for (int32_t sp = 1; sp <= smax; ++sp) {
     const double rounds = (double)((ts.tail * sp + slots - 1) / slots);
     const double cost = rounds * (1.0 / sp + 2.0 / mean_tiles);
@@ -1168,9 +1368,66 @@ static TailSplit tail_split(const sc_plan* p, const sc_cache* c, int32_t max_pie
 
 size_t attention_workspace_bytes(const sc_plan* p, const sc_cache* c) {
   if (c->d.dtype != SC_DTYPE_BF16 || p->nodes.empty()) return 0;
-  const TailSplit ts = tail_split(p, c);
-  if (ts.split == 1) return 0;
-  return (size_t)ts.tail * ts.split * ts.sh.bq * (HDB + 2) * sizeof(float);
+  return workspace_schedule(p, c).partial_bytes();
+}
+
+// The cheapest schedule whose partials fit `room` bytes, by estimated time in
+// us.  n is the units' mean length in 64-key tiles.  Measured (units of 12
+// heads, 64 .. 4680 queries, 256 .. 32760 keys, each form and split forced): a
+// unit takes
+//   256 queries, one work-group per CU   1.45 n + 6
+//   128 queries, two per CU              1.55 n + 8 together, 1.0 n + 6 alone
+//   64 queries                           2.0 n + 2.5
+// a round of pieces 7.6 us more (the partials' stores), the combine launch 4 us
+// and 0.22 us per MB of partials; keys over waves, 32 queries per work-group, 6.5
+// + 0.44 n per round and 1 in all.  So few units over short contexts go
+// to the waves form (one 64-query node over 1344 keys 17 us, 43 on the 64-query
+// form; 128 queries over 512 keys 10.6 us, 14.7), 256-query units that
+// leave half the CUs idle to 128-query ones (four nodes of 520 queries over 3640
+// keys 66 us, 104 in fifths), and long contexts stay where they were.
+static AttnSchedule attn_schedule(const sc_plan* p, const sc_cache* c, size_t room) {
+  const int32_t n = (int32_t)p->nodes.size();
+  int64_t keys = 0;
+  int32_t min_pages = INT32_MAX;
+  for (int32_t i = 0; i < n; ++i) {
+    const int32_t np = p->page_off[i + 1] - p->page_off[i];
+    keys += (int64_t)np * c->d.tokens_per_page;
+    min_pages = std::min(min_pages, np);
+  }
+  const double mean = (double)keys / n / 64.0;
+  const auto units_of = [&](int32_t bq) { return n * c->d.n_heads * ((p->nq + bq - 1) / bq); };
+  AttnSchedule best;
+  best.sh = AttnShape{WV_BQ, 1, 1};
+  best.whole = units_of(WV_BQ);
+  best.tail = 0;
+  best.split = 1;
+  double best_cost = (double)((best.whole + kCUs - 1) / kCUs) * (0.44 * mean + 6.5) + 1.0;
+  const AttnShape widest = attn_shape(p, c);
+  for (int32_t bq = widest.bq; bq >= std::min(widest.bq, BQ_SMALL); bq /= 2) {
+    AttnSchedule s;
+    s.sh = bq == widest.bq ? widest : AttnShape{bq, 2, 2};
+    const int32_t slots = kCUs * per_cu(s.sh), units = units_of(bq);
+    s.tail = units % slots;
+    s.whole = units - s.tail;
+    const double a = bq == BQ_MAX ? 1.45 : bq == BQ_SMALL ? 1.55 : 2.0, f = bq == BQ_MAX ? 6.0 : bq == BQ_SMALL ? 8.0 : 2.5;
+    const auto round = [&](int64_t items, double len) {  // the last, partly filled round
+      return bq == BQ_SMALL && items <= kCUs ? 1.0 * len + 6.0 : a * len + f;
+    };
+    const int32_t min_tiles = (int32_t)((int64_t)min_pages * c->d.tokens_per_page / (32 * s.sh.kh));
+    for (s.split = 1; s.split <= 16; ++s.split) {
+      if (s.split > 1 && (s.tail == 0 || s.split > min_tiles || s.partial_bytes() > room)) break;
+      const int64_t items = (int64_t)s.tail * s.split, full = items / slots, rest = items % slots;
+      const double len = mean / s.split;
+      double cost = (double)(s.whole / slots) * (a * mean + f) + (double)full * (a * len + f);
+      if (rest) cost += round(rest, len);
+      if (s.split > 1) cost += 7.6 * (double)items / slots + 4.0 + 0.22e-6 * (double)s.partial_bytes();
+      if (cost < best_cost - 1e-9) {
+        best_cost = cost;
+        best = s;
+      }
+    }
+  }
+  return best;
 }
 
 size_t attention_workspace_bound() { return (size_t)kAttnMaxPieces * BQ_MAX * (HDB + 2) * sizeof(float); }
@@ -1231,23 +1488,11 @@ static void shared_order(const sc_plan* p, AttnPlan& plan) {
   std::copy(p->attn_slot.begin(), p->attn_slot.end(), plan.page_slot);
 }
 
-// The launch of a plan whose split uses at most max_pieces pieces.
-static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t layer, const void* q,
-                                   void* o, float scale, void* ws, size_t ws_bytes, int32_t max_pieces,
-                                   hipStream_t stream);
-
-int launch_attention(const sc_plan* p, const sc_cache* c, int32_t layer, const void* q, void* o,
-                     float scale, void* ws, size_t ws_bytes, hipStream_t stream) {
-  return launch_attention_pieces(p, c, layer, q, o, scale, ws, ws_bytes, kAttnMaxPieces, stream);
-}
-
-static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t layer, const void* q,
-                                   void* o, float scale, void* ws, size_t ws_bytes, int32_t max_pieces,
-                                   hipStream_t stream) {
+// Launches a plan by a schedule (unused for fp32 caches).
+static int launch_scheduled(const sc_plan* p, const sc_cache* c, int32_t layer, const void* q, void* o,
+                            float scale, void* ws, const AttnSchedule& ts, hipStream_t stream) {
   const sc_cache_desc& d = c->d;
   const int32_t n = (int32_t)p->nodes.size();
-  const int rc = attention_check(p, c);
-  if (rc != SC_OK) return rc;
   AttnPlan plan;
   shared_order(p, plan);
   AttnGeom g;
@@ -1276,10 +1521,6 @@ static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t 
     SC_HIP(hipGetLastError());
     return SC_OK;
   }
-  const TailSplit ts = tail_split(p, c, max_pieces);
-  const size_t need = ts.split == 1 ? 0 : (size_t)ts.tail * ts.split * ts.sh.bq * (HDB + 2) * sizeof(float);
-  if (ws_bytes < need || (need && !ws))
-    return fail(SC_EINVAL, "attention workspace of %zu bytes, need %zu", ws_bytes, need);
   if (reinterpret_cast<uintptr_t>(ws) & 15) return fail(SC_EINVAL, "workspace must be 16-byte aligned");
   const int32_t bq = ts.sh.bq;
   g.n_qtiles = (p->nq + bq - 1) / bq;
@@ -1297,7 +1538,9 @@ static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t 
   uint16_t* ob = static_cast<uint16_t*>(o);
   timer_begin(TK_ATTENTION, stream);
   const int32_t ring = ts.sh.ring;
-  if (bq == BQ_TINY && ring == 4)
+  if (bq == WV_BQ)
+    hipLaunchKernelGGL(attn_waves_kernel, dim3(items), dim3(64 * WV_NW), 0, stream, qb, ob, g, plan);
+  else if (bq == BQ_TINY && ring == 4)
     hipLaunchKernelGGL((attn_bf16_kernel<2, 1, 4>), dim3(items), dim3(128), 0, stream, qb, ob, g, plan);
   else if (bq == BQ_TINY)
     hipLaunchKernelGGL((attn_bf16_kernel<2, 1, 3>), dim3(items), dim3(128), 0, stream, qb, ob, g, plan);
@@ -1319,6 +1562,17 @@ static int launch_attention_pieces(const sc_plan* p, const sc_cache* c, int32_t 
   }
   SC_HIP(hipGetLastError());
   return SC_OK;
+}
+
+int launch_attention(const sc_plan* p, const sc_cache* c, int32_t layer, const void* q, void* o,
+                     float scale, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const int rc = attention_check(p, c);
+  if (rc != SC_OK) return rc;
+  if (c->d.dtype == SC_DTYPE_F32) return launch_scheduled(p, c, layer, q, o, scale, ws, AttnSchedule{}, stream);
+  const size_t need = attention_workspace_bytes(p, c);
+  if (ws_bytes < need || (need && !ws))
+    return fail(SC_EINVAL, "attention workspace of %zu bytes, need %zu", ws_bytes, need);
+  return launch_scheduled(p, c, layer, q, o, scale, ws, attn_schedule(p, c, need), stream);
 }
 
 // ------------------------------------------------ attention without allocation
@@ -1364,15 +1618,7 @@ extern "C" int sc_attention_noalloc(const sc_plan* p, const sc_cache* c, int32_t
   if ((rc = attention_check(p, c)) != SC_OK) return rc;
   void* ptr = nullptr;
   if (c->d.dtype == SC_DTYPE_BF16 && (rc = scratch_address(&ptr)) != SC_OK) return rc;
-  // as many key-range pieces as the scratch holds partials for
-  const int32_t bq = attn_shape(p, c).bq;
-  const size_t piece_bytes = (size_t)bq * (HDB + 2) * sizeof(float);
-  const int32_t max_pieces = (int32_t)std::min<size_t>(kAttnMaxPieces, kNoAllocScratchBytes / piece_bytes);
-  const TailSplit ts = tail_split(p, c, max_pieces);
-  const size_t need = ts.split == 1 ? 0 : (size_t)ts.tail * ts.split * piece_bytes;
-  if (need > kNoAllocScratchBytes)
-    return fail(SC_ECAPACITY, "attention partials of %zu bytes exceed the %zu-byte scratch", need,
-                kNoAllocScratchBytes);
-  return launch_attention_pieces(p, c, layer, q, o, scale, ptr, ptr ? kNoAllocScratchBytes : 0, max_pieces,
-                                 static_cast<hipStream_t>(stream));
+  AttnSchedule ts{};
+  if (ptr) ts = attn_schedule(p, c, std::min(kNoAllocScratchBytes, attention_workspace_bytes(p, c)));
+  return launch_scheduled(p, c, layer, q, o, scale, ptr, ts, static_cast<hipStream_t>(stream));
 }

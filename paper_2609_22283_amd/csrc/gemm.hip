@@ -364,71 +364,6 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, 
   gemm_epilogue<EPI, UFB, 1, LDSB>(acc, pre, ep, F, T, fu * UF, tu * UT, lane, smem + wave * LDSB);
 }
 
-// N <= 4 copies of 1 KB each from memory straight into consecutive LDS: lane i
-// of copy j moves 16 bytes from biased + off[j] + 1024 j to lds + 1024 j + 16 i.
-// The instruction's offset field moves the memory and the LDS address alike, so
-// M0, which carries the LDS address, is set once for the group (and restored);
-// off[j] makes up for it (kCopyBias - 1024 j above the lane's own offset, the base kCopyBias
-// lower, so that it stays non-negative; rows come in multiples of 8 and are at
-// least 512 bytes long, so the sum stays below 2^32 for operands of up to 4 GB).
-// Written as inline asm: while a copy
-// it knows of is in flight, the compiler waits for every LDS fragment read with
-// lgkmcnt(0); not knowing of these, it counts the reads exactly.  The copies
-// complete under the ring's explicit vmcnt waits.
-constexpr uint32_t kCopyBias = 3072;
-template <int N>
-__device__ __forceinline__ void copy_group(const char* biased, const uint32_t* off, char* lds) {
-  const uint32_t l = (uint32_t)reinterpret_cast<uintptr_t>(lds);
-  uint32_t saved;
-  static_assert(N >= 1 && N <= 4, "copies per group");
-  if constexpr (N == 1)
-    asm volatile(
-        "s_mov_b32 %0, m0\n\t"
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %3, %1\n\t"
-        "s_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(biased), "s"(l), "v"(off[0])
-        : "memory");
-  else if constexpr (N == 2)
-    asm volatile(
-        "s_mov_b32 %0, m0\n\t"
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %3, %1\n\t"
-        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
-        "s_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1])
-        : "memory");
-  else if constexpr (N == 3)
-    asm volatile(
-        "s_mov_b32 %0, m0\n\t"
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %3, %1\n\t"
-        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
-        "global_load_lds_dwordx4 %5, %1 offset:2048\n\t"
-        "s_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1]), "v"(off[2])
-        : "memory");
-  else
-    asm volatile(
-        "s_mov_b32 %0, m0\n\t"
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %3, %1\n\t"
-        "global_load_lds_dwordx4 %4, %1 offset:1024\n\t"
-        "global_load_lds_dwordx4 %5, %1 offset:2048\n\t"
-        "global_load_lds_dwordx4 %6, %1 offset:3072\n\t"
-        "s_mov_b32 m0, %0"
-        : "=&s"(saved)
-        : "s"(biased), "s"(l), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3])
-        : "memory");
-}
-
 // Stage wait of the ring: all but this wave's N newest copies have landed and
 // its own fragment reads are done; then the same of every wave.
 template <int N>
@@ -483,6 +418,8 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
   const int32_t nk = Kd / GBK, kt0 = (int32_t)((int64_t)split * nk / S);
   const int32_t n = (int32_t)((int64_t)(split + 1) * nk / S) - kt0;  // stages of this part
 
+  // (rows come in multiples of 8 of at least 512 bytes, so the biased offsets
+  // stay below 2^32 for operands of up to 4 GB)
   uint32_t woff[NCW], xoff[NCX];
   const int32_t wg0 = NCW * wave, xg0 = NCX * wave - max(0, wave - XFULL);  // first row groups of this wave
 #pragma unroll
@@ -499,7 +436,7 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
   const char* xk = reinterpret_cast<const char*>(X) + (size_t)kt0 * GBK * 2 - kCopyBias;
   int32_t in_slot = 0;
   auto issue = [&]() __attribute__((always_inline)) {  // the next stage into the next slot
-    char* st = smem + in_slot;
+    const uint32_t st = (uint32_t)reinterpret_cast<uintptr_t>(smem) + in_slot;
     copy_group<NCW>(wk, woff, st + wg0 * 1024);
     if (XFULL == NW || wave < XFULL)
       copy_group<NCX>(xk, xoff, st + XO + xg0 * 1024);
