@@ -1375,11 +1375,11 @@ size_t attention_workspace_bytes(const sc_plan* p, const sc_cache* c) {
 // us.  n is the units' mean length in 64-key tiles.  Measured (units of 12
 // heads, 64 .. 4680 queries, 256 .. 32760 keys, each form and split forced): a
 // unit takes
-//   256 queries, one work-group per CU   1.45 n + 6
-//   128 queries, two per CU              1.55 n + 8 together, 1.0 n + 6 alone
+//   256 queries, one work-group per CU   1.5 n + 6
+//   128 queries, two per CU              1.6 n + 8 together, 1.05 n + 6 alone
 //   64 queries                           2.0 n + 2.5
-// a round of pieces 7.6 us more (the partials' stores), the combine launch 4 us
-// and 0.22 us per MB of partials; keys over waves, 32 queries per work-group, 6.5
+// a round of pieces 7 us more (the partials' stores), the combine launch 4 us
+// and 0.2 us per MB of partials; keys over waves, 32 queries per work-group, 6.5
 // + 0.44 n per round and 1 in all.  So few units over short contexts go
 // to the waves form (one 64-query node over 1344 keys 17 us, 43 on the 64-query
 // form; 128 queries over 512 keys 10.6 us, 14.7), 256-query units that
@@ -1409,9 +1409,9 @@ static AttnSchedule attn_schedule(const sc_plan* p, const sc_cache* c, size_t ro
     const int32_t slots = kCUs * per_cu(s.sh), units = units_of(bq);
     s.tail = units % slots;
     s.whole = units - s.tail;
-    const double a = bq == BQ_MAX ? 1.45 : bq == BQ_SMALL ? 1.55 : 2.0, f = bq == BQ_MAX ? 6.0 : bq == BQ_SMALL ? 8.0 : 2.5;
+    const double a = bq == BQ_MAX ? 1.5 : bq == BQ_SMALL ? 1.6 : 2.0, f = bq == BQ_MAX ? 6.0 : bq == BQ_SMALL ? 8.0 : 2.5;
     const auto round = [&](int64_t items, double len) {  // the last, partly filled round
-      return bq == BQ_SMALL && items <= kCUs ? 1.0 * len + 6.0 : a * len + f;
+      return bq == BQ_SMALL && items <= kCUs ? 1.05 * len + 6.0 : a * len + f;
     };
     const int32_t min_tiles = (int32_t)((int64_t)min_pages * c->d.tokens_per_page / (32 * s.sh.kh));
     for (s.split = 1; s.split <= 16; ++s.split) {
@@ -1420,7 +1420,7 @@ static AttnSchedule attn_schedule(const sc_plan* p, const sc_cache* c, size_t ro
       const double len = mean / s.split;
       double cost = (double)(s.whole / slots) * (a * mean + f) + (double)full * (a * len + f);
       if (rest) cost += round(rest, len);
-      if (s.split > 1) cost += 7.6 * (double)items / slots + 4.0 + 0.22e-6 * (double)s.partial_bytes();
+      if (s.split > 1) cost += 7.0 * (double)items / slots + 4.0 + 0.2e-6 * (double)s.partial_bytes();
       if (cost < best_cost - 1e-9) {
         best_cost = cost;
         best = s;
