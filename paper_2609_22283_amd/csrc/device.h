@@ -15,6 +15,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// the same for addresses that are only element-aligned (the hardware takes them)
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);

@@ -18,7 +18,9 @@ struct GemmEpilogue {
   // STORE / GELU / RESIDUAL: out[t * ld_out + f]
   uint16_t* out;
   int32_t ld_out;
-  // QKV
+  // QKV.  With w2, the sections are k and v only (F = 2 hidden): the k rows of
+  // W, then the rows of w2.
+  const uint16_t* w2;
   uint16_t* q_out;  // [T][hidden]
   char* layer_base;
   uint64_t slot_bytes, kv_half;
@@ -68,9 +70,10 @@ struct NormScale {
   uint16_t* rows;          // token-major [T][ld] rows (part offset 0), or NULL
   int32_t ld;
   const float* gain;       // [D] fp32 for rows, or NULL
-  char* layer_base;        // page-slot keys (part offset D / kSsPartWidth), or NULL
+  char* layer_base;        // page-slot keys, or NULL
   uint64_t slot_bytes;
   int32_t nq, tpp, ppc, head_dim;
+  int32_t k_part0;         // first partial of the keys in a token's row of part
   int32_t node_slot[kGemmMaxNodePages];
 };
 

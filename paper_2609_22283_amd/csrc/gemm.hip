@@ -138,8 +138,8 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
   if constexpr (EPI == EPI_QKV) {
     // a 256-feature tile lies in one of q, k, v (hidden is a multiple of 256)
     // and each wave's 128 or 64 features in one head (head_dim 128)
-    const int32_t sec = fw / ep.hidden;
-    const int32_t hf0 = fw - sec * ep.hidden;  // wave's first feature in its section
+    const int32_t part = fw / ep.hidden, sec = part + (ep.w2 ? 1 : 0);
+    const int32_t hf0 = fw - part * ep.hidden;  // wave's first feature in its section
     const int32_t head = hf0 / ep.head_dim;
     const int32_t dbase = hf0 - head * ep.head_dim + 4 * lg;
     if (ep.ss_part && sec < 2) {
@@ -191,7 +191,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
           uint16_t* vrow = reinterpret_cast<uint16_t*>(slot_base + ep.kv_half) +
                            ((size_t)head * ep.head_dim + d0 + pass * RP + row) * ep.tpp + n;
           if (t + 8 <= T) {
-            *reinterpret_cast<u32x4*>(vrow) = val;
+            *reinterpret_cast<u32x4u*>(vrow) = val;
           } else {  // a launch ending inside a run
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -258,7 +258,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
         if (sec == 0)
           *reinterpret_cast<u32x2*>(qrow + 16 * fb) = pk;
         else
-          *reinterpret_cast<u32x2*>(krow + d) = pk;
+          *reinterpret_cast<u32x2u*>(krow + d) = pk;
       }
     }
   } else {
@@ -420,19 +420,22 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
 
   // (rows come in multiples of 8 of at least 512 bytes, so the biased offsets
   // stay below 2^32 for operands of up to 4 GB)
+  // the weight rows of a section in a second matrix
+  const bool second = EPI == EPI_QKV && ep.w2 && f0 >= ep.hidden;
+  const int32_t w0 = f0 - (second ? ep.hidden : 0);
   uint32_t woff[NCW], xoff[NCX];
   const int32_t wg0 = NCW * wave, xg0 = NCX * wave - max(0, wave - XFULL);  // first row groups of this wave
 #pragma unroll
   for (int j = 0; j < NCW; ++j) {
     const int32_t row = 8 * (wg0 + j) + (lane >> 3);
-    woff[j] = ((uint32_t)(f0 + row) * Kd + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2 + kCopyBias - 1024 * j;
+    woff[j] = ((uint32_t)(w0 + row) * Kd + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2 + kCopyBias - 1024 * j;
   }
 #pragma unroll
   for (int j = 0; j < NCX; ++j) {
     const int32_t row = 8 * (xg0 + j) + (lane >> 3);
     xoff[j] = ((uint32_t)min(t0 + row, T - 1) * Kd + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2 + kCopyBias - 1024 * j;
   }
-  const char* wk = reinterpret_cast<const char*>(W) + (size_t)kt0 * GBK * 2 - kCopyBias;
+  const char* wk = reinterpret_cast<const char*>(EPI == EPI_QKV && second ? ep.w2 : W) + (size_t)kt0 * GBK * 2 - kCopyBias;
   const char* xk = reinterpret_cast<const char*>(X) + (size_t)kt0 * GBK * 2 - kCopyBias;
   int32_t in_slot = 0;
   auto issue = [&]() __attribute__((always_inline)) {  // the next stage into the next slot
@@ -681,7 +684,7 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
   if (F % GBM || Kd % GBK || T <= 0)
     return fail(SC_EUNSUPPORTED, "gemm needs F %% %d == 0, K %% %d == 0 (F=%d K=%d T=%d)", GBM, GBK,
                 F, Kd, T);
-  if ((uint64_t)F * Kd * 2 > 0xffffffffull || (uint64_t)T * Kd * 2 > 0xffffffffull)
+  if ((uint64_t)(ep.w2 ? F / 2 : F) * Kd * 2 > 0xffffffffull || (uint64_t)T * Kd * 2 > 0xffffffffull)
     return fail(SC_EUNSUPPORTED, "gemm operands beyond 4 GB");
   if (epi == EPI_QKV && (ep.hidden % GBM || ep.head_dim != 128))
     return fail(SC_EUNSUPPORTED, "QKV epilogue needs hidden %% %d == 0 and head_dim 128", GBM);
@@ -689,8 +692,9 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
   GemmEpilogue e = ep;
   if (epi == EPI_QKV) {
     // v goes out in 16-byte runs of 8 tokens within one page
+    // (condition caches may lie anywhere, as for sc_cache_append: the stores work unaligned too)
     if (ep.nq <= 0 || ep.tpp <= 0 || ep.grid_w <= 0 || ep.tpp % 8 || ep.nq % 8 || ep.slot_bytes % 16 ||
-        ep.kv_half % 16 || reinterpret_cast<uintptr_t>(ep.layer_base) % 16)
+        ep.kv_half % 16 || (!ep.w2 && reinterpret_cast<uintptr_t>(ep.layer_base) % 16))
       return fail(SC_EUNSUPPORTED, "QKV epilogue needs tpp and nq multiples of 8 and 16-byte aligned slots "
                   "(nq %d, tpp %d, grid_w %d)", ep.nq, ep.tpp, ep.grid_w);
     e.nq_div = magic_div((uint32_t)ep.nq);
@@ -779,7 +783,7 @@ __global__ __launch_bounds__(256) void norm_scale_kernel(int32_t T, NormScale ns
   if (t >= T) return;
   const int32_t np = ns.D / kSsPartWidth, nv = ns.D / 8;
   const float* pr = ns.part + (size_t)t * ns.n_part;
-  auto scale8 = [&](u32x4* p, float inv, const float* gain) {
+  auto scale8 = [&](u32x4u* p, float inv, const float* gain) {
     const u32x4 a = *p;
     float f[8];
 #pragma unroll
@@ -805,12 +809,12 @@ __global__ __launch_bounds__(256) void norm_scale_kernel(int32_t T, NormScale ns
     float s = 0.f;
     for (int32_t p = 0; p < np; ++p) s += pr[p];
     const float inv = rsqrtf(s / (float)ns.D + ns.eps);
-    u32x4* row = reinterpret_cast<u32x4*>(ns.rows + (size_t)t * ns.ld);
+    u32x4u* row = reinterpret_cast<u32x4u*>(ns.rows + (size_t)t * ns.ld);
     for (int32_t v = lane; v < nv; v += 64) scale8(row + v, inv, ns.gain ? ns.gain + 8 * v : nullptr);
   }
   if (ns.layer_base) {
     float s = 0.f;
-    for (int32_t p = 0; p < np; ++p) s += pr[np + p];
+    for (int32_t p = 0; p < np; ++p) s += pr[ns.k_part0 + p];
     const float inv = rsqrtf(s / (float)ns.D + ns.eps);
     const int32_t node = t / ns.nq, tok = t - node * ns.nq;
     const int32_t frame = tok / ns.tpp, n = tok - frame * ns.tpp;
@@ -819,7 +823,7 @@ __global__ __launch_bounds__(256) void norm_scale_kernel(int32_t T, NormScale ns
     const int32_t vph = ns.head_dim / 8;  // 16-byte vectors per head row
     for (int32_t v = lane; v < nv; v += 64) {
       const int32_t head = v / vph, c = v - head * vph;
-      scale8(reinterpret_cast<u32x4*>(kb + ((size_t)head * ns.tpp + n) * ns.head_dim + 8 * c), inv,
+      scale8(reinterpret_cast<u32x4u*>(kb + ((size_t)head * ns.tpp + n) * ns.head_dim + 8 * c), inv,
              nullptr);
     }
   }

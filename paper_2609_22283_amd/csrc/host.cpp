@@ -297,6 +297,24 @@ int sc_cache_release(sc_cache* c, sc_node st) {
   return SC_OK;
 }
 
+}  // extern "C"
+
+int sc::state_for_append(sc_cache* c, int32_t layer, StateKey key, StateEntry** e, bool* fresh) {
+  auto it = c->states.find(key);
+  if (it != c->states.end() && it->second.written[layer])
+    return fail(SC_EEXIST, "state (%d,%d) layer %d already written", key.first, key.second, layer);
+  *fresh = it == c->states.end();
+  if (*fresh) {
+    const int rc = allocate_state(c, key);
+    if (rc != SC_OK) return rc;
+    it = c->states.find(key);
+  }
+  *e = &it->second;
+  return SC_OK;
+}
+
+extern "C" {
+
 int sc_cache_append(sc_cache* c, int32_t layer, sc_node st, const void* k, const void* v,
                     const sc_rope* rope, sc_stream stream) {
   if (!c || !k || !v) return fail(SC_EINVAL, "null argument");
@@ -310,24 +328,16 @@ int sc_cache_append(sc_cache* c, int32_t layer, sc_node st, const void* k, const
     if ((st.chunk + 1) * c->d.pages_per_chunk > r.max_frames)
       return fail(SC_EINVAL, "chunk %d beyond the rope table's %d frames", st.chunk, r.max_frames);
   }
-  StateKey key(st.chunk, st.level);
-  auto it = c->states.find(key);
-  if (it != c->states.end() && it->second.written[layer])
-    return fail(SC_EEXIST, "state (%d,%d) layer %d already written", st.chunk, st.level, layer);
+  StateEntry* e = nullptr;
   bool fresh = false;
-  if (it == c->states.end()) {
-    int rc = allocate_state(c, key);
-    if (rc != SC_OK) return rc;
-    it = c->states.find(key);
-    fresh = true;
-  }
-  int rc = launch_append(c, layer, it->second.slots.data(), st.chunk, k, v, rope,
-                         static_cast<hipStream_t>(stream));
+  int rc = state_for_append(c, layer, StateKey(st.chunk, st.level), &e, &fresh);
+  if (rc != SC_OK) return rc;
+  rc = launch_append(c, layer, e->slots.data(), st.chunk, k, v, rope, static_cast<hipStream_t>(stream));
   if (rc != SC_OK) {
     if (fresh) sc_cache_release(c, st);
     return rc;
   }
-  set_written(c, it->second, layer, 1);
+  set_written(c, *e, layer, 1);
   return SC_OK;
 }
 

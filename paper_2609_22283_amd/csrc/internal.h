@@ -74,6 +74,10 @@ namespace sc {
 // written flags).  Returns SC_OK or an error code with the message set.
 int plan_check(const sc_plan* plan, const sc_cache* cache, int32_t layer);
 
+// The entry of a state about to be written at `layer`, its slots allocated if it
+// is new (*fresh: release it if the write fails).
+int state_for_append(sc_cache* cache, int32_t layer, StateKey key, StateEntry** e, bool* fresh);
+
 // Sets a state's written flag at `layer` and its slots' copies of it.
 void set_written(sc_cache* cache, StateEntry& e, int32_t layer, uint8_t v);
 
