@@ -15,7 +15,7 @@
 // 64 features, the first half of an RMSNorm over the feature axis (qk-norm);
 // norm_scale_kernel finishes it.  RESIDUAL can emit them for the rows it
 // writes, part-major; row_scale_kernel turns them into a row_scale.
-// Work-groups take tiles of the output (seven shapes, 256 x 256 down to
+// Work-groups take tiles of the output (eight shapes, 256 x 256 down to
 // 64 x 64) and, where the tiles alone would leave CUs idle, parts of the
 // contraction too; the parts' fp32 sums meet in gemm_reduce_kernel, which adds
 // them in order and runs the epilogue.  Operands go through an LDS ring of
@@ -586,13 +586,20 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
 }
 
 // The tile shapes: wide ones where the tiles fill the chip, narrow ones (the
-// last four) where wide tiles would leave CUs idle.
+// last five) where wide tiles would leave CUs idle.  At one work-group per CU a
+// narrow tile's time is its CU's copies into LDS (30 - 37 bytes per cycle), so
+// between 64 x 64 and 128 x 128 a 128 x 64 tile serves the launches that are a
+// little more than one round of the one and too few of the other: QKV of
+// 256 tokens x 1536 k 13.1 us, 14.8 and 17.8 on those; MLP-up of 192 tokens 12.0
+// us, 14.2 and 15.9.  (Five stages with one work-group per CU measured the same
+// alone on a CU and 21.6 us against 18.4 at 280 work-groups.)
 using Tile256 = GemmTile<256, 256, 2, 4, 1, 2, 2>;
 using Tile224 = GemmTile<256, 224, 4, 2, 1, 2, 2>;
 using Tile192 = GemmTile<256, 192, 4, 2, 1, 2, 2>;
 using Tile256x128 = GemmTile<256, 128, 4, 2, 1, 3, 2>;
 using Tile128 = GemmTile<128, 128, 2, 4, 1, 2, 4>;      // two work-groups per CU
 using Tile128Deep = GemmTile<128, 128, 2, 2, 2, 4, 2>;  // one per CU, a deeper ring
+using Tile128x64 = GemmTile<128, 64, 2, 2, 2, 3, 4>;    // two per CU
 using Tile64 = GemmTile<64, 64, 1, 2, 2, 5, 2>;         // two per CU
 
 // What a launch costs, in us, measured on the four projections of the
@@ -608,7 +615,7 @@ constexpr TileCost kTiles[] = {
     {256, 256, kCUs, 1.43, 10.2, 1.43, 10.2, 0.0},     {256, 224, kCUs, 1.34, 9.0, 1.34, 9.0, 0.0},
     {256, 192, kCUs, 1.11, 9.3, 1.11, 9.3, 0.0},       {256, 128, kCUs, 0.81, 6.2, 0.81, 6.2, 0.0},
     {128, 128, 2 * kCUs, 0.85, 5.7, 0.73, 4.0, 0.0},   {128, 128, kCUs, 0.46, 4.5, 0.46, 4.5, 0.0},
-    {64, 64, kCUs, 0.184, 0.6, 0.184, 0.6, 3.5},
+    {128, 64, 2 * kCUs, 0.48, 6.5, 0.262, 5.0, 0.0},   {64, 64, kCUs, 0.184, 0.6, 0.184, 0.6, 3.5},
 };
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 // Tile256's 128 x 64 wave tiles spill with these epilogues' state (104 and 96
@@ -639,9 +646,10 @@ static GemmShape gemm_shape(int epi, int32_t F, int32_t T, int32_t Kd, size_t pa
       const double n = (double)((nk + S - 1) / S);
       double cost = c.once + (double)full * (n * c.stage + c.fixed) + (S > 1 ? 3.5 + 0.2e-6 * bytes : 0.0);
       if (rest) cost += rest <= kCUs ? n * c.stage1 + c.fixed1 : n * c.stage + c.fixed;
-      // the QKV epilogue (RoPE, page scatter), exposed where no other
-      // work-group of the CU covers it: 2.5 - 4 us per round
-      if (epi == EPI_QKV && c.slots == kCUs) cost += 3.0 * (double)(full + (rest != 0));
+      // the QKV epilogue (RoPE, page scatter): 2.5 - 4 us per round where a
+      // CU holds one work-group, once where another's main loop covers it
+      // (64 x 64 tiles, 288 .. 864 work-groups: 3 us in all; two per CU: 1)
+      if (epi == EPI_QKV) cost += c.slots > kCUs ? 1.0 : c.once > 0.0 ? 3.0 : 3.0 * (double)(full + (rest != 0));
       if (cost < best_cost - 1e-9) {
         best_cost = cost;
         best = GemmShape{i, S};
@@ -671,6 +679,7 @@ static void launch_epi(GemmShape g, const uint16_t* W, const uint16_t* X, int32_
     case 3: launch_tile<EPI, Tile256x128>(W, X, F, T, Kd, g.split, ep, stream); break;
     case 4: launch_tile<EPI, Tile128>(W, X, F, T, Kd, g.split, ep, stream); break;
     case 5: launch_tile<EPI, Tile128Deep>(W, X, F, T, Kd, g.split, ep, stream); break;
+    case 6: launch_tile<EPI, Tile128x64>(W, X, F, T, Kd, g.split, ep, stream); break;
     default: launch_tile<EPI, Tile64>(W, X, F, T, Kd, g.split, ep, stream);
   }
   if (g.split > 1) {

@@ -1,6 +1,6 @@
 """The block's GEMMs over the sizes where their tile shape changes.
 
-launch_gemm picks one of seven tile shapes and a split of the contraction by
+launch_gemm picks one of eight tile shapes and a split of the contraction by
 size; the packs below (window 0: every node attends to itself) make the four
 projections take each of them, with token counts that end inside a tile and
 inside a 16-token block, and contractions whose parts differ by a stage.  The
@@ -32,14 +32,14 @@ DIMS, EPS = (44, 42, 42), 1e-6
 
 # heads, mlp, nodes, frames, grid_h, grid_w          tiles (rows x tokens, /parts) of QKV, out, up, down
 SIZES = [
-    (12, 8960, 1, 1, 4, 8),     # 32 tokens:     128x128/6, 64x64/8, 64x64, 64x64/10
-    (12, 8960, 1, 1, 8, 9),     # 72 tokens:     64x64, 64x64, 128x128 deep/3, 64x64/5
-    (12, 8960, 2, 1, 8, 13),    # 208 tokens:    128x128/3, 64x64, 128x128 deep, 128x128 deep/10
+    (12, 8960, 1, 1, 4, 8),     # 32 tokens:     128x64/6, 64x64/8, 64x64, 64x64/10
+    (12, 8960, 1, 1, 8, 9),     # 72 tokens:     64x64, 64x64, 128x64, 128x64/10
+    (12, 8960, 2, 1, 8, 13),    # 208 tokens:    128x64, 64x64, 128x128 deep, 128x128 deep/10
     (12, 8960, 1, 2, 11, 24),   # 528 tokens:    128x128 deep, 64x64, 256x128, 128x128 deep/4
-    (12, 8960, 1, 1, 25, 40),   # 1000 tokens:   128x128, 64x64, 256x192, 256x128/5
+    (12, 8960, 1, 1, 25, 40),   # 1000 tokens:   128x128, 128x64, 256x192, 256x128/5
     (12, 8960, 1, 3, 25, 40),   # 3000 tokens:   256x224, 256x128, 256x224, 256x224/3
     (12, 8960, 4, 3, 29, 40),   # 13920 tokens:  128x128, 256x192, 256x256, 256x192
-    (6, 3072, 1, 1, 8, 17),     # 136 tokens:    64x64, 64x64, 64x64, 64x64/7
+    (6, 3072, 1, 1, 8, 17),     # 136 tokens:    128x64, 64x64, 64x64, 64x64/7
 ]
 
 
