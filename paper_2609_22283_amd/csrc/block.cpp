@@ -19,7 +19,7 @@ static size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 
 constexpr float kNormEps = 1e-6f;
 
-// workspace: normalised input (or the folded RMSNorms' per-token factors) | q |
+// workspace: normalised input (or the folded RMSNorms' factors or sums of squares) | q |
 // attention output | MLP hidden | attention partials | partial sums of squares
 extern "C" size_t sc_block_workspace_bytes(const sc_block_weights* w, int32_t n_tokens) {
   if (!w || n_tokens <= 0) return 0;
@@ -57,9 +57,12 @@ static int cross_check(const sc_cross_attn* cr, const sc_cache* c, const sc_plan
   return plan_check(cr->plan, cr->cache, layer);
 }
 
-extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer,
-                                const sc_plan* p, void* x, const sc_rope* rope, void* ws,
-                                size_t ws_bytes, sc_stream stream_) {
+// The block; in a stack, sums_in says that the layer before left the sums of
+// squares of x's rows at the start of the workspace, sums_out asks for them of
+// the rows this one writes (see the folded RMSNorms below).
+int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
+                      const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, bool sums_out,
+                      sc_stream stream_) {
   if (!w || !c || !p || !x || !ws) return fail(SC_EINVAL, "null argument");
   if (!w->w_qkv || !w->w_o || !w->w_up || !w->w_down) return fail(SC_EINVAL, "null weight");
   const sc_cache_desc& d = c->d;
@@ -180,14 +183,28 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     ep.qk_gain = w->qk_norm;
   }
 
-  // Without modulation the pre-attention RMSNorm folds into the QKV GEMM:
-  // one pass over x writes each token's 1 / rms (into hn's region), and the
-  // QKV epilogue scales the token's accumulators by it, reading the raw rows.
+  // An RMSNorm without modulation folds into the GEMM that reads it: that one
+  // takes the raw rows and scales each token's accumulators by 1 / rms.  Where
+  // a residual GEMM wrote the rows, it stored their sums of squares (into hn's
+  // region, which holds nothing else then) and the folding GEMM reads these;
+  // the block's input takes a pass of its own for the factors.
+  float* const row_sums = reinterpret_cast<float*>(hn);
+  const auto emit_sums = [&](GemmEpilogue& e) {
+    e.ss_part = row_sums;
+    e.n_part = D / kSsPartWidth;
+  };
+  const auto fold_sums = [&](GemmEpilogue& e) {
+    e.row_part = row_sums;
+    e.row_eps = kNormEps;
+  };
   const uint16_t* qkv_in = hn;
   if (!w->mod) {
-    float* rsa = reinterpret_cast<float*>(hn);
-    if ((rc = launch_row_rms(xb, T, D, rsa, stream)) != SC_OK) return rc;
-    ep.row_scale = rsa;
+    if (sums_in) {
+      fold_sums(ep);
+    } else {
+      if ((rc = launch_row_rms(xb, T, D, row_sums, stream)) != SC_OK) return rc;
+      ep.row_scale = row_sums;
+    }
     qkv_in = xb;
   } else if ((rc = launch_rmsnorm(xb, hn, T, D, nm_a, stream)) != SC_OK) {
     return rc;
@@ -225,26 +242,18 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   e2.mod = w->mod;
   e2.gate_row = 2;  // gate_a
   for (int32_t i = 0; i < n; ++i) e2.node_level[i] = p->nodes[i].level;
-  // Without modulation the MLP's RMSNorm folds into its first GEMM: the last
-  // residual GEMM before it stores per-64-feature sums of squares of the rows
-  // it writes (part-major in ssb), a per-token kernel turns them into 1 / rms
-  // (into hn's region, unused then), and the GELU epilogue scales each
-  // token's accumulators by it, reading the raw rows x.
   const bool fold_mlp_norm = !w->mod;
-  if (fold_mlp_norm && !w->cross) e2.ss_part = ssb;
+  if (fold_mlp_norm || w->cross) emit_sums(e2);
   if ((rc = launch_gemm(EPI_RESIDUAL, TK_GEMM_OUT, static_cast<const uint16_t*>(w->w_o), ob, D, T, D, e2, stream)) != SC_OK)
     return rc;
   if (const sc_cross_attn* cr = w->cross) {
-    // the query's RMSNorm (no modulation) folded into its GEMM, the factors
-    // in hn's region (free once the QKV GEMM has read it)
-    float* rsq = reinterpret_cast<float*>(hn);
-    if ((rc = launch_row_rms(xb, T, D, rsq, stream)) != SC_OK) return rc;
+    // the query's RMSNorm has no modulation: folded into its GEMM
     GemmEpilogue ec;
     std::memset(&ec, 0, sizeof ec);
     scratch(ec);
     ec.out = qb;
     ec.ld_out = D;
-    ec.row_scale = rsq;
+    fold_sums(ec);
     if (cr->q_norm) {
       ec.ss_part = ssb;
       ec.n_part = D / kSsPartWidth;
@@ -275,7 +284,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     eo.out = xb;
     eo.ld_out = D;
     eo.nq = p->nq;
-    if (fold_mlp_norm) eo.ss_part = ssb;
+    if (fold_mlp_norm) emit_sums(eo);
     if ((rc = launch_gemm(EPI_RESIDUAL, TK_GEMM_CROSS_OUT, static_cast<const uint16_t*>(cr->w_o), ob, D, T, D, eo, stream)) != SC_OK)
       return rc;
   }
@@ -286,9 +295,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   e3.ld_out = w->mlp;
   const uint16_t* mlp_in = hn;
   if (fold_mlp_norm) {
-    float* rsb = reinterpret_cast<float*>(hn);
-    if ((rc = launch_row_scale(ssb, D / kSsPartWidth, T, D, kNormEps, rsb, stream)) != SC_OK) return rc;
-    e3.row_scale = rsb;
+    fold_sums(e3);
     mlp_in = xb;
   } else if ((rc = launch_rmsnorm(xb, hn, T, D, nm_m, stream)) != SC_OK) {
     return rc;
@@ -297,6 +304,7 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
     return rc;
   GemmEpilogue e4 = e2;
   e4.ss_part = nullptr;
+  if (sums_out) emit_sums(e4);
   e4.gate_row = 5;  // gate_m
   if ((rc = launch_gemm(EPI_RESIDUAL, TK_GEMM_DOWN, static_cast<const uint16_t*>(w->w_down), ub, D, T, w->mlp, e4, stream)) != SC_OK)
     return rc;
@@ -305,6 +313,12 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   for (int32_t i = 0; i < n; ++i)
     set_written(c, c->states.at(StateKey(p->nodes[i].chunk, p->nodes[i].level)), layer, 1);
   return SC_OK;
+}
+
+extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer,
+                                const sc_plan* p, void* x, const sc_rope* rope, void* ws,
+                                size_t ws_bytes, sc_stream stream) {
+  return block_forward(w, c, layer, p, x, rope, ws, ws_bytes, false, false, stream);
 }
 
 extern "C" size_t sc_condition_workspace_bytes(const sc_cache* c) {

@@ -38,15 +38,19 @@ struct GemmEpilogue {
   int32_t node_level[kGemmMaxNodes];
   // QKV, GELU and STORE with row_scale: an RMSNorm of the input rows folded
   // into the GEMM.  X holds the raw rows; each token's accumulators are
-  // multiplied by row_scale[t] (1 / rms of its row: launch_row_scale or
-  // launch_row_rms) before anything else of the epilogue.  NULL: none.
+  // multiplied by row_scale[t] (1 / rms of its row: launch_row_rms) before anything else of the epilogue.  NULL: none.
+  // With row_part instead, the work-group makes the factors itself from the
+  // sums of squares a RESIDUAL epilogue stored: 1 / sqrt(sum_p
+  // row_part[t * K / kSsPartWidth + p] / K + row_eps), in increasing p
+  // (16-byte aligned; K, the contraction, is the row's length).
   const float* row_scale;
+  const float* row_part;
+  float row_eps;
   // Sums of squares for a later RMSNorm over features (qk-norm), STORE and
   // QKV (q and k sections): ss_part[t * n_part + f / kSsPartWidth] = sum of
   // D[f'][t]^2 over the kSsPartWidth features f' of f's group, before any
-  // gain or RoPE.  RESIDUAL: the same over the updated rows as stored (bf16)
-  // but part-major, ss_part[(f / kSsPartWidth) * T + t], for an RMSNorm of
-  // the result folded into the next GEMM (n_part unused).
+  // gain or RoPE.  RESIDUAL: the same over the updated rows as stored (bf16),
+  // for an RMSNorm of the result folded into the next GEMM (its row_part).
   // NULL: none.  QKV with ss_part also multiplies q and k by qk_gain
   // ([2][hidden], the gains of q then k) before RoPE.
   float* ss_part;
@@ -95,11 +99,4 @@ int launch_rmsnorm(const uint16_t* x, uint16_t* y, int32_t rows, int32_t D, cons
 // themselves: scale[r] = 1 / sqrt(mean_f x[r][f]^2 + 1e-6) (a read of x,
 // no write of the normalised rows).  Feeds GemmEpilogue::row_scale.
 int launch_row_rms(const uint16_t* x, int32_t rows, int32_t D, float* scale, hipStream_t stream);
-// The second half of an RMSNorm without modulation or gain whose sums of
-// squares a RESIDUAL epilogue stored part-major: for t < T,
-//   scale[t] = 1 / sqrt(sum_{p < n_part} part[p * T + t] / D + eps),
-// summed in increasing p (deterministic).  Feeds GemmEpilogue::row_scale.
-int launch_row_scale(const float* part, int32_t n_part, int32_t T, int32_t D, float eps, float* scale,
-                     hipStream_t stream);
-
 }  // namespace sc

@@ -14,7 +14,7 @@
 // QKV and STORE can also emit per-token sums of squares over each group of
 // 64 features, the first half of an RMSNorm over the feature axis (qk-norm);
 // norm_scale_kernel finishes it.  RESIDUAL can emit them for the rows it
-// writes, part-major; row_scale_kernel turns them into a row_scale.
+// writes; the next GEMM's work-groups turn them into its row_scale.
 // Work-groups take tiles of the output (eight shapes, 256 x 256 down to
 // 64 x 64) and, where the tiles alone would leave CUs idle, parts of the
 // contraction too; the parts' fp32 sums meet in gemm_reduce_kernel, which adds
@@ -75,27 +75,46 @@ __device__ __forceinline__ void store_sum_squares(const f32x4 (&acc)[FB][TB], fl
     }
 }
 
-// What an epilogue reads besides the accumulators, loaded before the main loop
-// so that it lands during it.
-// RESIDUAL: the residual stream's out[t][f] (after the loop, every CU of the
-// launch would read its residual tile at once).  Rows past T read the last
-// row (valid memory, values unused).
-// The others: the folded RMSNorm's per-token factors; lane j loads those of
-// the wave's tokens j and j + 64 (two coalesced loads at most), and the
-// epilogue takes each token's from its lane.
-// (RESIDUAL on the widest tiles, above kEarlyResidual blocks of a wave: read in
-// the epilogue, since the registers would spill; out-projection at 18720 tokens
+// The folded RMSNorm's factor of token t: as it was stored (row_scale), or made
+// here from the row's sums of squares (row_part), which are read as whole 16-byte
+// runs, all in flight at once, and added in order.  (A launch of its own for that
+// between the two GEMMs took 4 - 5 us of every block, at 128 tokens and at 2376.)
+__device__ __forceinline__ float token_factor(const GemmEpilogue& ep, int32_t Kd, int32_t t) {
+  if (ep.row_scale) return ep.row_scale[t];
+  const int32_t nv = Kd / (4 * kSsPartWidth);
+  const f32x4* p = reinterpret_cast<const f32x4*>(ep.row_part) + (size_t)t * nv;
+  float s = 0.f;
+#pragma unroll 6
+  for (int32_t v = 0; v < nv; ++v) {
+    const f32x4 a = p[v];
+    s = (((s + a[0]) + a[1]) + a[2]) + a[3];
+  }
+  return rsqrtf(s * (1.0f / (float)Kd) + ep.row_eps);
+}
+
+// What an epilogue reads besides the accumulators, ready when the main loop ends.
+// RESIDUAL: the residual stream's out[t][f], loaded before the loop so that it
+// lands during it (after the loop, every CU of the launch would read its residual
+// tile at once).  Rows past T read the last row (valid memory, values unused).
+// (On the widest tiles, above kEarlyResidual blocks of a wave: read in the
+// epilogue, since the registers would spill; out-projection at 18720 tokens
 // on Tile224 90 us, 93 us with the early read.)
+// The others: the folded RMSNorm's per-token factors, fetched after the first
+// stages' copies are on their way.  Where several waves share tokens (SHARED),
+// the work-group's first threads fetch one each into LDS; else lane j takes
+// that of its wave's token j, and the epilogue takes each token's from its lane.
 constexpr int kEarlyResidual = 24;
-template <int EPI, int FB, int TB>
+template <int EPI, int FB, int TB, bool SHARED>
 struct EpiPre {
   static constexpr bool RES = EPI == EPI_RESIDUAL && FB * TB <= kEarlyResidual;
-  static constexpr int RT = EPI == EPI_RESIDUAL ? 1 : (16 * TB + 63) / 64;
+  static_assert(SHARED || EPI == EPI_RESIDUAL || TB <= 4, "a factor per lane");
   u32x2 res[RES ? TB : 1][RES ? FB : 1];
-  float rtok[RT];
-  __device__ __forceinline__ void load(const GemmEpilogue& ep, int32_t T, int32_t fw, int32_t tw, int32_t lane) {
-    const int32_t lg = lane >> 4, c16 = lane & 15;
+  float rtok;         // this lane's token's
+  const float* rows;  // SHARED: those of the wave's tokens
+  __device__ __forceinline__ void load_residual(const GemmEpilogue& ep, int32_t T, int32_t fw, int32_t tw,
+                                                int32_t lane) {
     if constexpr (RES) {
+      const int32_t lg = lane >> 4, c16 = lane & 15;
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
         const int32_t t = min(tw + 16 * tb + c16, T - 1);
@@ -103,10 +122,13 @@ struct EpiPre {
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) res[tb][fb] = *reinterpret_cast<const u32x2*>(orow + 16 * fb);
       }
-    } else if (EPI != EPI_RESIDUAL && ep.row_scale) {
-#pragma unroll
-      for (int r = 0; r < RT; ++r) rtok[r] = ep.row_scale[min(tw + 64 * r + lane, T - 1)];
     }
+  }
+  __device__ __forceinline__ float factor(int32_t tb, int32_t c16) const {
+    if constexpr (SHARED)
+      return rows[16 * tb + c16];
+    else
+      return __shfl(rtok, 16 * tb + c16);
   }
 };
 
@@ -114,20 +136,20 @@ struct EpiPre {
 // token tw: lane (lg, c16) holds D[f][t] for t = tw + 16 tb + c16 and
 // f = fw + 16 fb + 4 lg + e (e = 0..3) in acc[fb][tb][e].  lds: LDSB bytes
 // that no other wave touches any more.
-template <int EPI, int FB, int TB, int LDSB>
-__device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre<EPI, FB, TB>& pre,
+template <int EPI, int FB, int TB, int LDSB, bool SHARED>
+__device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre<EPI, FB, TB, SHARED>& pre,
                                               const GemmEpilogue& ep, int32_t F, int32_t T, int32_t fw,
                                               int32_t tw, int32_t lane, char* lds) {
   constexpr int WM = 16 * FB, GWN = 16 * TB;
   const int32_t lg = lane >> 4, c16 = lane & 15;
   // The folded RMSNorm of the input rows: D is linear in the row, so the
-  // token's 1 / rms scales its accumulators before anything else (taken
-  // from the lane that loaded it while every lane is active).
+  // token's 1 / rms scales its accumulators before anything else (while
+  // every lane is active: it may come from another lane).
   if constexpr (EPI != EPI_RESIDUAL) {
-    if (ep.row_scale) {
+    if (ep.row_scale || ep.row_part) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
-        const float r = __shfl(pre.rtok[tb >> 2], 16 * (tb & 3) + c16);
+        const float r = pre.factor(tb, c16);
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
@@ -292,7 +314,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
               for (int e = 0; e < 4; ++e) v[e] *= gv[e];
             }
             u32x2 r;
-            if constexpr (EpiPre<EPI, FB, TB>::RES)
+            if constexpr (EpiPre<EPI, FB, TB, SHARED>::RES)
               r = pre.res[tb][fb];
             else
               r = *reinterpret_cast<const u32x2*>(dst);
@@ -320,7 +342,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
           float sq = ssq[g];
           sq += __shfl_xor(sq, 16);
           sq += __shfl_xor(sq, 32);
-          if (lg == 0) ep.ss_part[(size_t)((fw) / kSsPartWidth + g) * T + t] = sq;
+          if (lg == 0) ep.ss_part[(size_t)t * ep.n_part + fw / kSsPartWidth + g] = sq;
         }
       }
     }
@@ -342,7 +364,8 @@ __device__ __forceinline__ f32x4* part_unit(const GemmEpilogue& ep, int32_t spli
 // small sizes (4 us of 13.6 at 128 tokens x 8960 k in five parts), then by the
 // partials' traffic (9 us for 29 MB).
 template <int EPI>
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, int32_t S, GemmEpilogue ep) {
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, int32_t Kd, int32_t S,
+                                                          GemmEpilogue ep) {
   constexpr int LDSB = UF * (UT + 8) * 2;  // the v transpose of the QKV epilogue
   __shared__ __attribute__((aligned(16))) char smem[EPI == EPI_QKV ? 4 * LDSB : 16];
   const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -350,8 +373,10 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, 
   const int32_t u = blockIdx.x * 4 + wave;
   if (u >= n_fu * n_tu) return;
   const int32_t fu = u / n_tu, tu = u - fu * n_tu;
-  EpiPre<EPI, UFB, 1> pre;
-  pre.load(ep, T, fu * UF, tu * UT, lane);
+  EpiPre<EPI, UFB, 1, false> pre;
+  pre.load_residual(ep, T, fu * UF, tu * UT, lane);
+  if (EPI != EPI_RESIDUAL && (ep.row_scale || ep.row_part))
+    pre.rtok = token_factor(ep, Kd, min(tu * UT + (lane & 15), T - 1));
   f32x4 acc[UFB][1];
 #pragma unroll
   for (int fb = 0; fb < UFB; ++fb) acc[fb][0] = f32x4{};
@@ -361,7 +386,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(int32_t F, int32_t T, 
   for (int32_t s = 0; s < S; ++s, p += stride)
 #pragma unroll
     for (int fb = 0; fb < UFB; ++fb) acc[fb][0] += p[fb * 64];
-  gemm_epilogue<EPI, UFB, 1, LDSB>(acc, pre, ep, F, T, fu * UF, tu * UT, lane, smem + wave * LDSB);
+  gemm_epilogue<EPI, UFB, 1, LDSB, false>(acc, pre, ep, F, T, fu * UF, tu * UT, lane, smem + wave * LDSB);
 }
 
 // Stage wait of the ring: all but this wave's N newest copies have landed and
@@ -398,6 +423,10 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
   // stage s: weight rows at s * STAGE, token rows XO further; rows of 64 k
   // (128 B) with 16-byte column c stored at c ^ ((row >> 1) & 7)
   __shared__ __attribute__((aligned(1024))) char smem[D * STAGE];
+  // (not where it would cost a work-group's place on the CU: 64 x 64 tiles fill the LDS)
+  constexpr bool SHARED = EPI != EPI_RESIDUAL && WF > 1;
+  static_assert(!SHARED || BN <= 64 * NW, "a thread per token");
+  __shared__ float row_factor[SHARED ? BN : 1];
   const int32_t n_tf = F / BM, n_tt = (T + BN - 1) / BN, n_tiles = n_tf * n_tt;
   // Each XCD takes a contiguous run of logical items (all tiles of one part of
   // the contraction, then the next part); the tiles are walked in groups of GT
@@ -450,11 +479,18 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
     in_slot = in_slot + STAGE == D * STAGE ? 0 : in_slot + STAGE;
   };
   const int32_t tw = t0 + wt + 16 * TBO * kw;  // first token of the blocks this wave finishes
-  EpiPre<EPI, FB, TBO> pre;
-  if (S == 1) pre.load(ep, T, f0 + wf, tw, lane);
+  EpiPre<EPI, FB, TBO, SHARED> pre;
+  pre.rows = row_factor + (tw - t0);
+  if (S == 1) pre.load_residual(ep, T, f0 + wf, tw, lane);
 #pragma unroll
   for (int j = 0; j < D - 1; ++j)
     if (j < n) issue();
+  if (EPI != EPI_RESIDUAL && S == 1 && (ep.row_scale || ep.row_part)) {
+    if constexpr (!SHARED)
+      pre.rtok = token_factor(ep, Kd, min(tw + lane % (16 * TBO), T - 1));
+    else if (tid < BN)  // the ring's barriers stand between this and the epilogue
+      row_factor[tid] = token_factor(ep, Kd, min(t0 + tid, T - 1));
+  }
 
   // 16x16x32 MFMAs: lane (lg, c16) supplies row c16 of each 16-row operand
   // block with k values 8 lg .. 8 lg + 7 of a 32-k step
@@ -582,7 +618,7 @@ __global__ __launch_bounds__(64 * C::WF * C::WT * C::KW, C::WPE) void gemm_bf16_
   }
   constexpr int LDSB = KW == 1 ? D * STAGE / NW : OWN * 1024;
   if (KW == 1 && EPI == EPI_QKV) __syncthreads();  // every wave is done with the ring: v is staged in it
-  gemm_epilogue<EPI, FB, TBO, LDSB>(sum, pre, ep, F, T, f0 + wf, tw, lane, smem + wave * LDSB);
+  gemm_epilogue<EPI, FB, TBO, LDSB, SHARED>(sum, pre, ep, F, T, f0 + wf, tw, lane, smem + wave * LDSB);
 }
 
 // The tile shapes: wide ones where the tiles fill the chip, narrow ones (the
@@ -684,7 +720,7 @@ static void launch_epi(GemmShape g, const uint16_t* W, const uint16_t* X, int32_
   }
   if (g.split > 1) {
     const uint32_t units = (uint32_t)(F / UF) * (uint32_t)((T + UT - 1) / UT);
-    hipLaunchKernelGGL((gemm_reduce_kernel<EPI>), dim3((units + 3) / 4), dim3(256), 0, stream, F, T, g.split, ep);
+    hipLaunchKernelGGL((gemm_reduce_kernel<EPI>), dim3((units + 3) / 4), dim3(256), 0, stream, F, T, Kd, g.split, ep);
   }
 }
 
@@ -697,7 +733,7 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
     return fail(SC_EUNSUPPORTED, "gemm operands beyond 4 GB");
   if (epi == EPI_QKV && (ep.hidden % GBM || ep.head_dim != 128))
     return fail(SC_EUNSUPPORTED, "QKV epilogue needs hidden %% %d == 0 and head_dim 128", GBM);
-  if (ep.row_scale && epi == EPI_RESIDUAL) return fail(SC_EINVAL, "row_scale is not a RESIDUAL epilogue input");
+  if ((ep.row_scale || ep.row_part) && epi == EPI_RESIDUAL) return fail(SC_EINVAL, "row_scale is not a RESIDUAL epilogue input");
   GemmEpilogue e = ep;
   if (epi == EPI_QKV) {
     // v goes out in 16-byte runs of 8 tokens within one page
@@ -868,30 +904,6 @@ int launch_row_rms(const uint16_t* x, int32_t rows, int32_t D, float* scale, hip
   hipLaunchKernelGGL(rmsnorm_kernel, dim3((rows + 3) / 4), dim3(256), 0, stream, x, nullptr, scale, rows, D,
                      1e-6f, plain);
   timer_end(TK_RMSNORM, stream);
-  SC_HIP(hipGetLastError());
-  return SC_OK;
-}
-
-// One thread per token; partial p of all tokens is contiguous, so each of
-// the n_part loads of a wave reads 256 consecutive bytes.  Unrolled so that
-// eight loads are in flight at once; the adds keep increasing p.
-__global__ __launch_bounds__(256) void row_scale_kernel(const float* __restrict__ part, int32_t n_part, int32_t T,
-                                                        float inv_d, float eps, float* __restrict__ scale) {
-  const int32_t t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  float s = 0.f;
-#pragma unroll 8
-  for (int32_t p = 0; p < n_part; ++p) s += part[(size_t)p * T + t];
-  scale[t] = rsqrtf(s * inv_d + eps);
-}
-
-int launch_row_scale(const float* part, int32_t n_part, int32_t T, int32_t D, float eps, float* scale,
-                     hipStream_t stream) {
-  if (T <= 0 || n_part <= 0 || D <= 0) return fail(SC_EINVAL, "row_scale needs T, n_part, D > 0");
-  timer_begin(TK_ROW_SCALE, stream);
-  hipLaunchKernelGGL(row_scale_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, part, n_part, T,
-                     1.0f / (float)D, eps, scale);
-  timer_end(TK_ROW_SCALE, stream);
   SC_HIP(hipGetLastError());
   return SC_OK;
 }

@@ -110,6 +110,12 @@ int launch_append(const sc_cache* cache, int32_t layer, const int32_t* slots, in
                   const void* k, const void* v, const sc_rope* rope, hipStream_t stream);
 int launch_rope_table(const sc_rope_desc* d, void* table, hipStream_t stream);
 
+// sc_block_forward as one layer of a stack: sums_in: the sums of squares of x's
+// rows lie at the start of ws (the layer before left them); sums_out: leave
+// those of the rows written there.
+int block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
+                  const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, bool sums_out, sc_stream stream);
+
 // Kernel timer: launchers bracket their kernel with timer_begin/timer_end.
 enum TimerKind {
   TK_ATTENTION = 0, TK_GEMM_QKV, TK_GEMM_OUT, TK_GEMM_UP, TK_GEMM_DOWN, TK_RMSNORM, TK_APPEND,

@@ -73,7 +73,10 @@ extern "C" int sc_stack_forward(const sc_block_weights* layers, int32_t n_layers
   if (!cache || n_layers > cache->d.n_layers)
     return fail(SC_EINVAL, "%d layers but the cache holds %d", n_layers, cache ? cache->d.n_layers : 0);
   for (int32_t l = 0; l < n_layers; ++l) {
-    int rc = sc_block_forward(&layers[l], cache, l, plan, x, rope, ws, ws_bytes, stream);
+    // a layer without modulation folds its first RMSNorm in from the sums of
+    // squares that the layer before it stored with its rows
+    const bool sums_in = l > 0 && !layers[l].mod, sums_out = l + 1 < n_layers && !layers[l + 1].mod;
+    int rc = block_forward(&layers[l], cache, l, plan, x, rope, ws, ws_bytes, sums_in, sums_out, stream);
     if (rc != SC_OK) {
       // layers before l are complete, but the forward as a whole is not:
       // mark none of the pack's layers written so the caller can rerun it
