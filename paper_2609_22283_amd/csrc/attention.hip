@@ -1123,9 +1123,54 @@ __device__ __forceinline__ void copies_landed() {
 // This wave's LDS reads are done: what they read may be copied over.
 __device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Ranges that the work-groups past the attention's own read and drop (ReadAhead).
+// A few dozen of these work-groups take 10 - 18 us and leave most CUs without
+// one, while the launches after them wait for weights from HBM: blocks whose
+// weights were read last 450 MB ago, 128 tokens with a condition 122.9 -> 113.2
+// us, 256 tokens 100.0 -> 94.0, 384 tokens 98.9 -> 94.6, 64 tokens 81.5 -> 78.8,
+// a four-layer stream 2.81 -> 2.72 ms.  It costs 3 us where the weights lie in the
+// memory-side cache already (one block called over and over: 99.1 -> 102.9,
+// 81.0 -> 84.3).  5 MB per us of the attention's time but its first 3 us: 4 or 6
+// MB per us measured within 1 us, 2 MB 2 - 4 us slower.
+constexpr double kAheadBytesPerUs = 5.0e6, kAheadLostUs = 3.0;
+struct AttnAhead {
+  const char* p[ReadAhead::kMax];
+  uint32_t vecs[ReadAhead::kMax];  // 16-byte vectors
+  int32_t n, units;                // work-groups of the attention itself
+};
+
+// Bound by HBM: eight loads of a thread in flight, 64 KB per work-group.
+__device__ __forceinline__ void read_ahead(const AttnAhead& a) {
+  const uint32_t threads = (gridDim.x - (uint32_t)a.units) * (64 * WV_NW);
+  const uint32_t first = (blockIdx.x - (uint32_t)a.units) * (64 * WV_NW) + threadIdx.x;
+  for (int32_t r = 0; r < a.n; ++r) {
+    const u32x4u* p = reinterpret_cast<const u32x4u*>(a.p[r]);
+    const uint32_t n = a.vecs[r];
+    for (uint32_t i = first; i < n; i += 8 * threads) {
+      u32x4 v[8];
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) v[j] = p[min(i + j * threads, n - 1)];
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) asm volatile("" ::"v"(v[j]));
+    }
+  }
+}
+
+struct NoAhead {};
+
+// Ahead: AttnAhead, or NoAhead where nothing is to be read.
+template <class Ahead>
 __global__ __launch_bounds__(64 * WV_NW, 2) void attn_waves_kernel(const uint16_t* __restrict__ q,
                                                                    uint16_t* __restrict__ o, AttnGeom g,
-                                                                   AttnPlan plan) {
+                                                                   AttnPlan plan, Ahead ahead) {
+  uint32_t units = gridDim.x;
+  if constexpr (std::is_same_v<Ahead, AttnAhead>) {
+    units = (uint32_t)ahead.units;
+    if (blockIdx.x >= units) {
+      read_ahead(ahead);
+      return;
+    }
+  }
   __shared__ __attribute__((aligned(1024))) char smem[WV_RED];
   __shared__ float ml[2][WV_NW][WV_BQ];
   using KV = WaveTiles;
@@ -1133,7 +1178,7 @@ __global__ __launch_bounds__(64 * WV_NW, 2) void attn_waves_kernel(const uint16_
   const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t lg = lane >> 4, c = lane & 15;
   // query tiles fastest: an XCD's work-groups share the K/V of a few (node, head)s
-  const int32_t unit = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
+  const int32_t unit = (int32_t)xcd_remap(blockIdx.x, units);
   const int32_t qt = unit % g.n_qtiles, nh = unit / g.n_qtiles;
   const int32_t node = nh % g.n_nodes, head = nh / g.n_nodes;
   const KV kv(plan, g, node, head, lane);
@@ -1318,6 +1363,7 @@ static AttnShape attn_shape(const sc_plan* p, const sc_cache* c) {
 struct AttnSchedule {
   AttnShape sh;
   int32_t whole, tail, split;
+  double us;  // estimated time (attn_schedule)
   size_t partial_bytes() const {
     return split == 1 ? 0 : (size_t)tail * split * sh.bq * (HDB + 2) * sizeof(float);
   }
@@ -1427,7 +1473,31 @@ static AttnSchedule attn_schedule(const sc_plan* p, const sc_cache* c, size_t ro
       }
     }
   }
+  best.us = best_cost;
   return best;
+}
+
+// What a keys-over-waves launch of `units` work-groups reads ahead, on a
+// work-group per CU that it leaves idle: as many bytes as these fetch in the
+// time the attention takes anyway.
+static AttnAhead take_ahead(int32_t units, double us) {
+  AttnAhead a;
+  std::memset(&a, 0, sizeof a);
+  a.units = units;
+  ReadAhead* const ra = ReadAhead::current;
+  if (!ra || units >= kCUs) return a;
+  double room = kAheadBytesPerUs * std::min(1.0, (kCUs - units) / 128.0) * (us - kAheadLostUs);
+  while (ra->next < ra->n && room >= 65536.0) {
+    ReadAhead::Range& r = ra->range[ra->next];
+    const size_t take = std::min(r.bytes, (size_t)room / 16 * 16);
+    a.p[a.n] = r.p;
+    a.vecs[a.n++] = (uint32_t)(take / 16);
+    r.p += take;
+    r.bytes -= take;
+    room -= (double)take;
+    if (r.bytes < 16) ++ra->next;
+  }
+  return a;
 }
 
 size_t attention_workspace_bound() { return (size_t)kAttnMaxPieces * BQ_MAX * (HDB + 2) * sizeof(float); }
@@ -1538,9 +1608,15 @@ static int launch_scheduled(const sc_plan* p, const sc_cache* c, int32_t layer, 
   uint16_t* ob = static_cast<uint16_t*>(o);
   timer_begin(TK_ATTENTION, stream);
   const int32_t ring = ts.sh.ring;
-  if (bq == WV_BQ)
-    hipLaunchKernelGGL(attn_waves_kernel, dim3(items), dim3(64 * WV_NW), 0, stream, qb, ob, g, plan);
-  else if (bq == BQ_TINY && ring == 4)
+  if (bq == WV_BQ) {
+    const AttnAhead ahead = take_ahead((int32_t)items, ts.us);
+    if (ahead.n)
+      hipLaunchKernelGGL((attn_waves_kernel<AttnAhead>), dim3(kCUs), dim3(64 * WV_NW), 0, stream, qb, ob, g, plan,
+                         ahead);
+    else
+      hipLaunchKernelGGL((attn_waves_kernel<NoAhead>), dim3(items), dim3(64 * WV_NW), 0, stream, qb, ob, g, plan,
+                         NoAhead{});
+  } else if (bq == BQ_TINY && ring == 4)
     hipLaunchKernelGGL((attn_bf16_kernel<2, 1, 4>), dim3(items), dim3(128), 0, stream, qb, ob, g, plan);
   else if (bq == BQ_TINY)
     hipLaunchKernelGGL((attn_bf16_kernel<2, 1, 3>), dim3(items), dim3(128), 0, stream, qb, ob, g, plan);

@@ -58,11 +58,11 @@ static int cross_check(const sc_cross_attn* cr, const sc_cache* c, const sc_plan
 }
 
 // The block; in a stack, sums_in says that the layer before left the sums of
-// squares of x's rows at the start of the workspace, sums_out asks for them of
-// the rows this one writes (see the folded RMSNorms below).
+// squares of x's rows at the start of the workspace, and this one leaves those of
+// the rows it writes for the next (see the folded RMSNorms below).
 int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
-                      const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, bool sums_out,
-                      sc_stream stream_) {
+                      const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in,
+                      const sc_block_weights* next, sc_stream stream_) {
   if (!w || !c || !p || !x || !ws) return fail(SC_EINVAL, "null argument");
   if (!w->w_qkv || !w->w_o || !w->w_up || !w->w_down) return fail(SC_EINVAL, "null weight");
   const sc_cache_desc& d = c->d;
@@ -230,6 +230,15 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
     std::memcpy(ns.node_slot, ep.node_slot, sizeof ns.node_slot);
     if ((rc = launch_norm_scale(T, ns, stream)) != SC_OK) return rc;
   }
+  ReadAhead ahead;
+  ahead.add(w->w_o, (size_t)D * D * 2);
+  if (w->cross) {
+    ahead.add(w->cross->w_q, (size_t)D * D * 2);
+    ahead.add(w->cross->w_o, (size_t)D * D * 2);
+  }
+  ahead.add(w->w_up, (size_t)w->mlp * D * 2);
+  ahead.add(w->w_down, (size_t)w->mlp * D * 2);
+  if (next && next->hidden == D) ahead.add(next->w_qkv, (size_t)3 * D * D * 2);
   if ((rc = launch_attention(p, c, layer, qb, ob, 1.0f / std::sqrt((float)d.head_dim), attn_ws,
                              attention_workspace_bound(), stream)) != SC_OK)
     return rc;
@@ -304,7 +313,7 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
     return rc;
   GemmEpilogue e4 = e2;
   e4.ss_part = nullptr;
-  if (sums_out) emit_sums(e4);
+  if (next && !next->mod) emit_sums(e4);
   e4.gate_row = 5;  // gate_m
   if ((rc = launch_gemm(EPI_RESIDUAL, TK_GEMM_DOWN, static_cast<const uint16_t*>(w->w_down), ub, D, T, w->mlp, e4, stream)) != SC_OK)
     return rc;
@@ -318,7 +327,7 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
 extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer,
                                 const sc_plan* p, void* x, const sc_rope* rope, void* ws,
                                 size_t ws_bytes, sc_stream stream) {
-  return block_forward(w, c, layer, p, x, rope, ws, ws_bytes, false, false, stream);
+  return block_forward(w, c, layer, p, x, rope, ws, ws_bytes, false, nullptr, stream);
 }
 
 extern "C" size_t sc_condition_workspace_bytes(const sc_cache* c) {

@@ -111,10 +111,34 @@ int launch_append(const sc_cache* cache, int32_t layer, const int32_t* slots, in
 int launch_rope_table(const sc_rope_desc* d, void* table, hipStream_t stream);
 
 // sc_block_forward as one layer of a stack: sums_in: the sums of squares of x's
-// rows lie at the start of ws (the layer before left them); sums_out: leave
-// those of the rows written there.
+// rows lie at the start of ws (the layer before left them); next: the layer
+// after it, or NULL.
 int block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
-                  const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, bool sums_out, sc_stream stream);
+                  const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, const sc_block_weights* next,
+                  sc_stream stream);
+
+// Memory that the launches after an attention will read first, in their order:
+// weights, which a model of many layers finds in HBM every time.  While an object
+// of this kind lives, this thread's launch_attention calls may take ranges off its
+// front and have compute units that the attention leaves idle read them, so
+// that they lie in the memory-side cache.  Nothing but time depends on it.
+struct ReadAhead {
+  static constexpr int kMax = 6;
+  struct Range {
+    const char* p;
+    size_t bytes;
+  } range[kMax];
+  int n = 0, next = 0;
+  ReadAhead* const outer;
+  static inline thread_local ReadAhead* current = nullptr;
+  ReadAhead() : outer(current) { current = this; }
+  ~ReadAhead() { current = outer; }
+  ReadAhead(const ReadAhead&) = delete;
+  ReadAhead& operator=(const ReadAhead&) = delete;
+  void add(const void* p, size_t bytes) {
+    if (n < kMax) range[n++] = Range{static_cast<const char*>(p), bytes};
+  }
+};
 
 // Kernel timer: launchers bracket their kernel with timer_begin/timer_end.
 enum TimerKind {

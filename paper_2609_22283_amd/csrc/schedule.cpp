@@ -75,8 +75,9 @@ extern "C" int sc_stack_forward(const sc_block_weights* layers, int32_t n_layers
   for (int32_t l = 0; l < n_layers; ++l) {
     // a layer without modulation folds its first RMSNorm in from the sums of
     // squares that the layer before it stored with its rows
-    const bool sums_in = l > 0 && !layers[l].mod, sums_out = l + 1 < n_layers && !layers[l + 1].mod;
-    int rc = block_forward(&layers[l], cache, l, plan, x, rope, ws, ws_bytes, sums_in, sums_out, stream);
+    const bool sums_in = l > 0 && !layers[l].mod;
+    const sc_block_weights* next = l + 1 < n_layers ? &layers[l + 1] : nullptr;
+    int rc = block_forward(&layers[l], cache, l, plan, x, rope, ws, ws_bytes, sums_in, next, stream);
     if (rc != SC_OK) {
       // layers before l are complete, but the forward as a whole is not:
       // mark none of the pack's layers written so the caller can rerun it
