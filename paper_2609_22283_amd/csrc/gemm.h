@@ -38,7 +38,8 @@ struct GemmEpilogue {
   int32_t node_level[kGemmMaxNodes];
   // QKV, GELU and STORE with row_scale: an RMSNorm of the input rows folded
   // into the GEMM.  X holds the raw rows; each token's accumulators are
-  // multiplied by row_scale[t] (1 / rms of its row: launch_row_rms) before anything else of the epilogue.  NULL: none.
+  // multiplied by row_scale[t] (1 / rms of its row: launch_row_rms) before
+  // anything else of the epilogue.  NULL: none.
   // With row_part instead, the work-group makes the factors itself from the
   // sums of squares a RESIDUAL epilogue stored: 1 / sqrt(sum_p
   // row_part[t * K / kSsPartWidth + p] / K + row_eps), in increasing p
