@@ -1126,12 +1126,11 @@ __device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0
 // Ranges that the work-groups past the attention's own read and drop (ReadAhead).
 // A few dozen of these work-groups take 10 - 18 us and leave most CUs without
 // one, while the launches after them wait for weights from HBM: blocks whose
-// weights were read last 450 MB ago, 128 tokens with a condition 122.9 -> 113.2
-// us, 256 tokens 100.0 -> 94.0, 384 tokens 98.9 -> 94.6, 64 tokens 81.5 -> 78.8,
-// a four-layer stream 2.81 -> 2.72 ms.  It costs 3 us where the weights lie in the
-// memory-side cache already (one block called over and over: 99.1 -> 102.9,
-// 81.0 -> 84.3).  5 MB per us of the attention's time but its first 3 us: 4 or 6
-// MB per us measured within 1 us, 2 MB 2 - 4 us slower.
+// weights were read last 450 MB ago, 128 tokens with a condition 122.7 -> 111.4
+// us, 256 tokens 99.6 -> 91.9, a four-layer stream 2.81 -> 2.71 ms.  It costs 1 us
+// where the weights lie in the memory-side cache already (one block called over
+// and over: 81.0 -> 81.9).  5 MB per us of the attention's time but its first 3
+// us: 4 or 6 MB per us measured within 1 us, 2 MB 2 - 4 us slower.
 constexpr double kAheadBytesPerUs = 5.0e6, kAheadLostUs = 3.0;
 struct AttnAhead {
   const char* p[ReadAhead::kMax];
@@ -1139,19 +1138,18 @@ struct AttnAhead {
   int32_t n, units;                // work-groups of the attention itself
 };
 
-// Bound by HBM: eight loads of a thread in flight, 64 KB per work-group.
+// Two loads of a thread in flight, 16 KB per work-group: enough for the rate
+// above.  Eight crowd the attention's own copies out (256 tokens 94.0 us against
+// 91.9, and 84.2 against 81.9 with the weights in the cache already).
 __device__ __forceinline__ void read_ahead(const AttnAhead& a) {
   const uint32_t threads = (gridDim.x - (uint32_t)a.units) * (64 * WV_NW);
   const uint32_t first = (blockIdx.x - (uint32_t)a.units) * (64 * WV_NW) + threadIdx.x;
   for (int32_t r = 0; r < a.n; ++r) {
     const u32x4u* p = reinterpret_cast<const u32x4u*>(a.p[r]);
     const uint32_t n = a.vecs[r];
-    for (uint32_t i = first; i < n; i += 8 * threads) {
-      u32x4 v[8];
-#pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) v[j] = p[min(i + j * threads, n - 1)];
-#pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) asm volatile("" ::"v"(v[j]));
+    for (uint32_t i = first; i < n; i += 2 * threads) {
+      const u32x4 a = p[i], b = p[min(i + threads, n - 1)];
+      asm volatile("" ::"v"(a), "v"(b));
     }
   }
 }
