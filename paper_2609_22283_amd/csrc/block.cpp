@@ -57,12 +57,10 @@ static int cross_check(const sc_cross_attn* cr, const sc_cache* c, const sc_plan
   return plan_check(cr->plan, cr->cache, layer);
 }
 
-// The block; in a stack, sums_in says that the layer before left the sums of
-// squares of x's rows at the start of the workspace, and this one leaves those of
-// the rows it writes for the next (see the folded RMSNorms below).
-int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
-                      const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in,
-                      const sc_block_weights* next, sc_stream stream_) {
+// Everything that is refused before a launch: the arguments of a block, its limits
+// and the states that it reads and writes at `layer`.
+int sc::block_check(const sc_block_weights* w, const sc_cache* c, int32_t layer, const sc_plan* p, const void* x,
+                    const sc_rope* rope, const void* ws, size_t ws_bytes) {
   if (!w || !c || !p || !x || !ws) return fail(SC_EINVAL, "null argument");
   if (!w->w_qkv || !w->w_o || !w->w_up || !w->w_down) return fail(SC_EINVAL, "null weight");
   const sc_cache_desc& d = c->d;
@@ -88,13 +86,6 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
         return fail(SC_EINVAL, "node (%d,%d) has no row in a %d-level modulation table",
                     p->nodes[i].chunk, p->nodes[i].level, w->mod_levels);
   }
-  NormMod nm_a;
-  std::memset(&nm_a, 0, sizeof nm_a);
-  nm_a.mod = w->mod;
-  nm_a.nq = p->nq;
-  for (int32_t i = 0; i < n; ++i) nm_a.node_level[i] = p->nodes[i].level;
-  NormMod nm_m = nm_a;
-  nm_m.which = 1;
   if (ws_bytes < sc_block_workspace_bytes(w, T))
     return fail(SC_EINVAL, "workspace of %zu bytes, need %zu", ws_bytes, sc_block_workspace_bytes(w, T));
   if (misaligned16(ws)) return fail(SC_EINVAL, "workspace must be 16-byte aligned");
@@ -110,8 +101,6 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
   }
   // pages of states the pack does not produce must be written at this layer;
   // the pack's own states must not be (they are written here)
-  GemmEpilogue ep;
-  std::memset(&ep, 0, sizeof ep);
   for (int32_t i = 0; i < n; ++i) {
     auto it = c->states.find(StateKey(p->nodes[i].chunk, p->nodes[i].level));
     if (it == c->states.end())
@@ -121,9 +110,6 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
                   p->nodes[i].level, layer);
     if (rope && (p->nodes[i].chunk + 1) * d.pages_per_chunk > rope->desc.max_frames)
       return fail(SC_EINVAL, "chunk %d beyond the rope table", p->nodes[i].chunk);
-    ep.node_chunk[i] = p->nodes[i].chunk;
-    for (int32_t f = 0; f < d.pages_per_chunk; ++f)
-      ep.node_slot[i * d.pages_per_chunk + f] = it->second.slots[f];
   }
   for (size_t q = 0; q < p->page_slot.size(); ++q) {
     int32_t s = p->page_slot[q];
@@ -135,6 +121,35 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
       if (p->nodes[i].chunk == key.first && p->nodes[i].level == key.second) in_pack = true;
     if (!in_pack && !c->states.at(key).written[layer])
       return fail(SC_EUNAVAILABLE, "state (%d,%d) has no K/V at layer %d", key.first, key.second, layer);
+  }
+  return SC_OK;
+}
+
+// The launches of a block whose arguments block_check has accepted; in a stack,
+// sums_in says that the layer before left the sums of squares of x's rows at the
+// start of the workspace, and this one leaves those of the rows it writes for the
+// next (see the folded RMSNorms below).
+int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
+                      const sc_rope* rope, void* ws, bool sums_in, const sc_block_weights* next,
+                      sc_stream stream_) {
+  const sc_cache_desc& d = c->d;
+  const int32_t n = (int32_t)p->nodes.size();
+  if (n == 0) return SC_OK;
+  const int32_t T = n * p->nq;
+  int rc;
+  NormMod nm_a;
+  std::memset(&nm_a, 0, sizeof nm_a);
+  nm_a.mod = w->mod;
+  nm_a.nq = p->nq;
+  for (int32_t i = 0; i < n; ++i) nm_a.node_level[i] = p->nodes[i].level;
+  NormMod nm_m = nm_a;
+  nm_m.which = 1;
+  GemmEpilogue ep;
+  std::memset(&ep, 0, sizeof ep);
+  for (int32_t i = 0; i < n; ++i) {
+    const StateEntry& e = c->states.at(StateKey(p->nodes[i].chunk, p->nodes[i].level));
+    ep.node_chunk[i] = p->nodes[i].chunk;
+    for (int32_t f = 0; f < d.pages_per_chunk; ++f) ep.node_slot[i * d.pages_per_chunk + f] = e.slots[f];
   }
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -238,7 +253,7 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
   }
   ahead.add(w->w_up, (size_t)w->mlp * D * 2);
   ahead.add(w->w_down, (size_t)w->mlp * D * 2);
-  if (next && next->hidden == D) ahead.add(next->w_qkv, (size_t)3 * D * D * 2);
+  if (next) ahead.add(next->w_qkv, (size_t)3 * D * D * 2);
   if ((rc = launch_attention(p, c, layer, qb, ob, 1.0f / std::sqrt((float)d.head_dim), attn_ws,
                              attention_workspace_bound(), stream)) != SC_OK)
     return rc;
@@ -327,7 +342,8 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
 extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer,
                                 const sc_plan* p, void* x, const sc_rope* rope, void* ws,
                                 size_t ws_bytes, sc_stream stream) {
-  return block_forward(w, c, layer, p, x, rope, ws, ws_bytes, false, nullptr, stream);
+  const int rc = block_check(w, c, layer, p, x, rope, ws, ws_bytes);
+  return rc != SC_OK ? rc : block_forward(w, c, layer, p, x, rope, ws, false, nullptr, stream);
 }
 
 extern "C" size_t sc_condition_workspace_bytes(const sc_cache* c) {

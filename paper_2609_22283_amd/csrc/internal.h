@@ -110,12 +110,14 @@ int launch_append(const sc_cache* cache, int32_t layer, const int32_t* slots, in
                   const void* k, const void* v, const sc_rope* rope, hipStream_t stream);
 int launch_rope_table(const sc_rope_desc* d, void* table, hipStream_t stream);
 
-// sc_block_forward as one layer of a stack: sums_in: the sums of squares of x's
-// rows lie at the start of ws (the layer before left them); next: the layer
-// after it, or NULL.
+// sc_block_forward in two halves: what it refuses, and its launches (whose
+// arguments have passed the first).  As one layer of a stack: sums_in: the sums of
+// squares of x's rows lie at the start of ws (the layer before left them); next:
+// the layer after it, checked too (its weights may be read ahead), or NULL.
+int block_check(const sc_block_weights* w, const sc_cache* c, int32_t layer, const sc_plan* p, const void* x,
+                const sc_rope* rope, const void* ws, size_t ws_bytes);
 int block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, const sc_plan* p, void* x,
-                  const sc_rope* rope, void* ws, size_t ws_bytes, bool sums_in, const sc_block_weights* next,
-                  sc_stream stream);
+                  const sc_rope* rope, void* ws, bool sums_in, const sc_block_weights* next, sc_stream stream);
 
 // Memory that the launches after an attention will read first, in their order:
 // weights, which a model of many layers finds in HBM every time.  While an object

@@ -72,12 +72,18 @@ extern "C" int sc_stack_forward(const sc_block_weights* layers, int32_t n_layers
   if (!layers || n_layers < 1) return fail(SC_EINVAL, "need at least one layer");
   if (!cache || n_layers > cache->d.n_layers)
     return fail(SC_EINVAL, "%d layers but the cache holds %d", n_layers, cache ? cache->d.n_layers : 0);
+  // every layer is checked before the first launch: a layer's launches may
+  // already read the next one's weights (ReadAhead)
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const int rc = block_check(&layers[l], cache, l, plan, x, rope, ws, ws_bytes);
+    if (rc != SC_OK) return rc;
+  }
   for (int32_t l = 0; l < n_layers; ++l) {
     // a layer without modulation folds its first RMSNorm in from the sums of
     // squares that the layer before it stored with its rows
     const bool sums_in = l > 0 && !layers[l].mod;
     const sc_block_weights* next = l + 1 < n_layers ? &layers[l + 1] : nullptr;
-    int rc = block_forward(&layers[l], cache, l, plan, x, rope, ws, ws_bytes, sums_in, next, stream);
+    int rc = block_forward(&layers[l], cache, l, plan, x, rope, ws, sums_in, next, stream);
     if (rc != SC_OK) {
       // layers before l are complete, but the forward as a whole is not:
       // mark none of the pack's layers written so the caller can rerun it

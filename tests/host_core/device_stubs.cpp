@@ -3,12 +3,14 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer.  No kernel runs: every
 // launcher only counts its call, and fails with SC_EDEVICE on the call
 // numbered g_fail_at (1-based), so the driver can force an error at any
-// point of a block's launch sequence.
+// point of a block's launch sequence.  The attention also notes what it is
+// given to read ahead.
 #include "../../paper_2609_22283_amd/csrc/gemm.h"
 #include "../../paper_2609_22283_amd/csrc/internal.h"
 
 int g_launches = 0;
 int g_fail_at = -1;
+std::vector<std::vector<const void*>> g_ahead;  // per attention launch: the ranges left to read ahead
 
 namespace sc {
 
@@ -20,6 +22,10 @@ static int launched(const char* what) {
 
 int launch_attention(const sc_plan*, const sc_cache*, int32_t, const void*, void*, float, void*, size_t,
                      hipStream_t) {
+  std::vector<const void*> left;
+  if (const ReadAhead* ra = ReadAhead::current)
+    for (int r = ra->next; r < ra->n; ++r) left.push_back(ra->range[r].p);
+  g_ahead.push_back(left);
   return launched("attention");
 }
 int attention_check(const sc_plan*, const sc_cache*) { return SC_OK; }

@@ -7,7 +7,9 @@
 // the schedule (Eq. 7 rounds, Eq. 2 serial order, the release rule), and the
 // block and stack orchestration's error paths: a launch failing at any point
 // of a block leaves the pack's states unwritten, and a stack failing in its
-// second layer leaves the first layer unwritten too.  Also the magic
+// second layer leaves the first layer unwritten too; a stack whose later layer
+// is invalid is refused before any launch (a launch may already read that
+// layer's weights ahead).  Also the magic
 // dividers the kernels split token indices with: exact quotients for every
 // divisor up to 4096 and the workload's own.  Exit status 0 when every check
 // holds; the sanitizers abort on the first memory or UB error.
@@ -22,6 +24,7 @@
 
 extern int g_launches;
 extern int g_fail_at;
+extern std::vector<std::vector<const void*>> g_ahead;
 
 static int g_failed = 0;
 #define CHECK(cond)                                                      \
@@ -293,6 +296,57 @@ static void test_block_error_paths() {
   }
 }
 
+// A stack's later layers are checked before its first launch, whose attention
+// is already handed the next layer's weights.
+static void test_stack_checks_every_layer_first() {
+  sc_policy p = policy(SC_POLICY_PROG, 4, 6);
+  sc_node pack[2] = {{0, 3}, {1, 4}};
+  Cache cc(3, 40);
+  sc_selection* sel = nullptr;
+  sc_plan* plan = nullptr;
+  CHECK(sc_selection_build(&p, pack, 2, &sel) == SC_OK);
+  CHECK(sc_plan_build(sel, cc.c, &plan) == SC_OK);
+  sc_selection_free(sel);
+  sc_block_weights good[3] = {weights(512), weights(512), weights(512)};
+  good[1].w_qkv = fake(0x64000000);
+  good[2].w_qkv = fake(0x65000000);
+  const size_t ws = sc_block_workspace_bytes(&good[0], 2 * 312);
+  static const float gain[1] = {1.f};
+  sc_cross_attn no_plan;
+  std::memset(&no_plan, 0, sizeof no_plan);
+  const auto refused = [&](int at, int code, auto&& spoil) {
+    sc_block_weights w[3] = {good[0], good[1], good[2]};
+    spoil(w[at]);
+    g_launches = 0;
+    g_ahead.clear();
+    CHECK(sc_stack_forward(w, 3, cc.c, plan, fake(0x70000000), nullptr, fake(0x80000000), ws, nullptr) == code);
+    CHECK(g_launches == 0 && g_ahead.empty());
+    for (auto& nd : pack)
+      for (int l = 0; l < 3; ++l) CHECK(sc_cache_contains(cc.c, nd, l) == 0);
+  };
+  for (int at = 0; at < 3; ++at) {
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.w_qkv = nullptr; });
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.w_o = nullptr; });
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.w_down = nullptr; });
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.n_heads = 4; });
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.hidden = 512; });
+    refused(at, SC_EUNSUPPORTED, [](sc_block_weights& w) { w.mlp = 320; });
+    refused(at, SC_EINVAL, [](sc_block_weights& w) { w.mlp = 1024; });  // a larger workspace
+    refused(at, SC_EINVAL, [&](sc_block_weights& w) { w.mod = gain; });  // no rows for the pack's levels
+    refused(at, SC_EINVAL, [&](sc_block_weights& w) { w.cross = &no_plan; });
+  }
+  g_launches = 0;
+  g_ahead.clear();
+  CHECK(sc_stack_forward(good, 3, cc.c, plan, fake(0x70000000), nullptr, fake(0x80000000), ws, nullptr) == SC_OK);
+  CHECK(g_ahead.size() == 3);
+  for (int l = 0; l < 3 && l < (int)g_ahead.size(); ++l) {
+    std::vector<const void*> want = {good[l].w_o, good[l].w_up, good[l].w_down};
+    if (l < 2) want.push_back(good[l + 1].w_qkv);
+    CHECK(g_ahead[l] == want);
+  }
+  sc_plan_free(plan);
+}
+
 // The quotient as the kernels form it: (high 32 bits of n * mul, + n) >> shift.
 static uint32_t magic_quotient(uint32_t n, const sc::DivMagic& m) {
   const uint32_t hi = (uint32_t)(((uint64_t)n * m.mul) >> 32);
@@ -337,6 +391,7 @@ int main() {
   test_cache_and_plan();
   test_schedule();
   test_block_error_paths();
+  test_stack_checks_every_layer_first();
   if (g_failed) {
     std::fprintf(stderr, "%d check(s) failed\n", g_failed);
     return 1;
