@@ -296,6 +296,7 @@ int sc::block_forward(const sc_block_weights* w, sc_cache* c, int32_t layer, con
       ns.gain = cr->q_norm;
       if ((rc = launch_norm_scale(T, ns, stream)) != SC_OK) return rc;
     }
+    ahead.passed(2);  // w_o and w_q: their GEMMs are behind this attention
     {
       TimerAlias alias(TK_ATTENTION, TK_CROSS_ATTENTION);
       if ((rc = launch_attention(cr->plan, cr->cache, layer, qb, ob, 1.0f / std::sqrt((float)d.head_dim),

@@ -140,6 +140,10 @@ struct ReadAhead {
   void add(const void* p, size_t bytes) {
     if (n < kMax) range[n++] = Range{static_cast<const char*>(p), bytes};
   }
+  // The first k ranges have been read by launches already enqueued.
+  void passed(int k) {
+    if (next < k) next = k;
+  }
 };
 
 // Kernel timer: launchers bracket their kernel with timer_begin/timer_end.

@@ -11,6 +11,7 @@
 int g_launches = 0;
 int g_fail_at = -1;
 std::vector<std::vector<const void*>> g_ahead;  // per attention launch: the ranges left to read ahead
+int g_take = 0;                                 // ranges that an attention launch takes off the front
 
 namespace sc {
 
@@ -23,8 +24,10 @@ static int launched(const char* what) {
 int launch_attention(const sc_plan*, const sc_cache*, int32_t, const void*, void*, float, void*, size_t,
                      hipStream_t) {
   std::vector<const void*> left;
-  if (const ReadAhead* ra = ReadAhead::current)
+  if (ReadAhead* ra = ReadAhead::current) {
     for (int r = ra->next; r < ra->n; ++r) left.push_back(ra->range[r].p);
+    ra->next = ra->next + g_take < ra->n ? ra->next + g_take : ra->n;
+  }
   g_ahead.push_back(left);
   return launched("attention");
 }

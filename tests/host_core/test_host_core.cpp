@@ -13,6 +13,7 @@
 // dividers the kernels split token indices with: exact quotients for every
 // divisor up to 4096 and the workload's own.  Exit status 0 when every check
 // holds; the sanitizers abort on the first memory or UB error.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -25,6 +26,7 @@
 extern int g_launches;
 extern int g_fail_at;
 extern std::vector<std::vector<const void*>> g_ahead;
+extern int g_take;
 
 static int g_failed = 0;
 #define CHECK(cond)                                                      \
@@ -297,8 +299,8 @@ static void test_block_error_paths() {
 }
 
 // A stack's later layers are checked before its first launch, whose attention
-// is already handed the next layer's weights.
-static void test_stack_checks_every_layer_first() {
+// is already handed the next layer's weights; what each attention is handed.
+static void test_stack_checks_and_read_ahead() {
   sc_policy p = policy(SC_POLICY_PROG, 4, 6);
   sc_node pack[2] = {{0, 3}, {1, 4}};
   Cache cc(3, 40);
@@ -345,6 +347,41 @@ static void test_stack_checks_every_layer_first() {
     CHECK(g_ahead[l] == want);
   }
   sc_plan_free(plan);
+
+  // with a cross-attention: it is offered what its own launch and the
+  // following ones read, whatever the self-attention took before it
+  Cache cond(3, 3);
+  cond.append_all_layers({0, 0});
+  sc_node conds[2] = {{0, 0}, {0, 0}};
+  sc_cross_attn cross;
+  std::memset(&cross, 0, sizeof cross);
+  cross.w_q = fake(0x66000000);
+  cross.w_o = fake(0x67000000);
+  cross.cache = cond.c;
+  sc_plan* plan_c = nullptr;
+  CHECK(sc_plan_condition(cond.c, conds, 2, 312, &plan_c) == SC_OK);
+  cross.plan = plan_c;
+  for (auto& w : good) w.cross = &cross;
+  for (int take = 0; take <= 6; ++take) {
+    Cache c2(3, 40);
+    CHECK(sc_selection_build(&p, pack, 2, &sel) == SC_OK);
+    CHECK(sc_plan_build(sel, c2.c, &plan) == SC_OK);
+    g_ahead.clear();
+    g_take = take;
+    CHECK(sc_stack_forward(good, 3, c2.c, plan, fake(0x70000000), nullptr, fake(0x80000000), ws, nullptr) == SC_OK);
+    CHECK(g_ahead.size() == 6);
+    for (size_t a = 0; a < g_ahead.size(); ++a) {
+      const size_t l = a / 2;
+      std::vector<const void*> all = {good[l].w_o, cross.w_q, cross.w_o, good[l].w_up, good[l].w_down};
+      if (l < 2) all.push_back(good[l + 1].w_qkv);
+      const size_t first = a % 2 == 0 ? 0 : std::min(all.size(), std::max((size_t)2, (size_t)take));
+      CHECK(g_ahead[a] == std::vector<const void*>(all.begin() + first, all.end()));
+    }
+    sc_plan_free(plan);
+    sc_selection_free(sel);
+  }
+  g_take = 0;
+  sc_plan_free(plan_c);
 }
 
 // The quotient as the kernels form it: (high 32 bits of n * mul, + n) >> shift.
@@ -391,7 +428,7 @@ int main() {
   test_cache_and_plan();
   test_schedule();
   test_block_error_paths();
-  test_stack_checks_every_layer_first();
+  test_stack_checks_and_read_ahead();
   if (g_failed) {
     std::fprintf(stderr, "%d check(s) failed\n", g_failed);
     return 1;
