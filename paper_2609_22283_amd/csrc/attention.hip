@@ -98,7 +98,8 @@ __global__ __launch_bounds__(64 * F32_NW) void attn_f32_kernel(const float* __re
   const int32_t t_end = (int32_t)((int64_t)(wave + 1) * nt / F32_NW);
   int32_t t = (int32_t)((int64_t)wave * nt / F32_NW), page = t / tp, tt = t - page * tp;
   // K rows of keys past the page's end read its last key, V^T runs past it
-  // the page's first tokens (valid memory; their probabilities are zero)
+  // the page's first tokens (valid memory); their probabilities are zero, and
+  // so are these V^T values, since an infinity there would make 0 x inf
   auto load_k = [&](f32x4 (&kf)[NJ]) {
     const float* kb = reinterpret_cast<const float*>(g.layer_base + (size_t)plan.page_slot[p0 + page] * g.slot_bytes) +
                       ((size_t)head * g.tpp + min(F32_BK * tt + c, g.tpp - 1)) * HD + 4 * lg;
@@ -118,6 +119,7 @@ __global__ __launch_bounds__(64 * F32_NW) void attn_f32_kernel(const float* __re
 #pragma unroll
       for (int j = 0; j < NJ; ++j) vf[j] = *reinterpret_cast<const f32x4u*>(vb + (size_t)16 * j * g.tpp);
     }
+    const bool page_end = F32_BK * tt + F32_BK > g.tpp;
     f32x4 s0 = {}, s1 = {};
 #pragma unroll
     for (int j = 0; j < NJ; j += 2)
@@ -150,6 +152,9 @@ __global__ __launch_bounds__(64 * F32_NW) void attn_f32_kernel(const float* __re
 #pragma unroll
     for (int e = 0; e < 4; ++e) p[e] = expf(s[e] - ms);
     l += (p[0] + p[1]) + (p[2] + p[3]);
+    if (page_end && k0 >= g.tpp)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) vf[j] = f32x4{};
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import paper_2609_22283_amd as sc
+from synth import normal
 from synth.configs import Geometry
 
 from gpu_cases import AttnCase, F32_MAX_ABS
@@ -39,3 +40,26 @@ def test_f32_tiles(heads, head_dim, grid, frames, window, kind, n):
         want = case.oracle(i)
         assert np.abs(out[i] - want).max() <= F32_MAX_ABS, pack[i]
         assert np.linalg.norm(out[i] - want) <= F32_REL * np.linalg.norm(want), pack[i]
+
+
+@pytest.mark.parametrize("head_dim,grid,frames", [(128, (8, 13), 3), (64, (1, 8), 1), (128, (5, 8), 2)])
+def test_f32_infinite_values(head_dim, grid, frames):
+    """A channel of +inf in every value row stays +inf where pages end inside a
+    16-key tile: the masked half of that tile reads real tokens' values at
+    weight zero, and 0 x inf would be NaN.  The other channels stay right."""
+    geo = Geometry(heads=2, head_dim=head_dim, grid_h=grid[0], grid_w=grid[1], frames_per_chunk=frames, K=4, W=2,
+                   rope_dims=(44, 42, 42) if head_dim == 128 else (24, 20, 20))
+    assert geo.tokens_per_page % 16 == 8
+
+    def value_fn(st):
+        v = normal((geo.tokens_per_chunk, geo.heads, head_dim), (17, 3) + tuple(st))
+        v[:, :, 5] = np.inf
+        return v
+
+    case = AttnCase(geo, sc.SC_DTYPE_F32, "same", [(2, 2), (3, 2)], [(0, 2), (1, 2)], seed=17, value_fn=value_fn)
+    out = case.run()
+    rest = np.arange(head_dim) != 5
+    for i in range(2):
+        assert np.all(out[i][:, :, 5] == np.inf), i
+        want = case.oracle(i)[:, :, rest]
+        assert np.abs(out[i][:, :, rest] - want).max() <= F32_MAX_ABS, i
