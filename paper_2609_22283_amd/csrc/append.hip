@@ -153,8 +153,9 @@ __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ k, co
 #pragma unroll
       for (int j = 0; j < N / 2; ++j) {
         const float x0 = f[2 * j], x1 = f[2 * j + 1];
-        f[2 * j] = x0 * cs[i][j].x - x1 * cs[i][j].y;
-        f[2 * j + 1] = x0 * cs[i][j].y + x1 * cs[i][j].x;
+        // written out, so that a key's bits do not hang on how the compiler contracts these
+        f[2 * j] = fmaf(x0, cs[i][j].x, -(x1 * cs[i][j].y));
+        f[2 * j + 1] = fmaf(x0, cs[i][j].y, x1 * cs[i][j].x);
       }
       kv[i] = Vec<T>::st(f);
     }

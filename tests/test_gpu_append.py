@@ -62,6 +62,41 @@ def test_append(dtype, heads, hd, gh, gw, frames, rotated, shift):
     assert raw[shift * size + nbytes:].eq(0xFF).all() and raw[:shift * size].eq(0xFF).all()  # nothing outside the pool
 
 
+@pytest.mark.parametrize("hd", [128, 64])
+def test_append_rotation_bits(hd):
+    """Rotated fp32 keys bit by bit: k0' = k0 c - [k1 s] and k1' = k0 s + [k1 c] with
+    the bracketed product rounded to fp32 and the rest once (a fused multiply-add),
+    so that cached keys stay the same from one build of the kernel to the next.
+    In 64 bits that is a product and a sum of 24-bit values, rounded to fp32 at
+    the end: the intermediate rounding at 53 bits changes the result only where
+    it lands on a tie, about 2^-29 of the values."""
+    torch = torch_mod()
+    dims = (44, 42, 42) if hd == 128 else (24, 20, 20)
+    heads, gh, gw, frames, chunk = 2, 5, 8, 2, 3
+    tpp, n = gh * gw, gh * gw * frames
+    args = (1, heads, hd, tpp, frames, frames, sc.SC_DTYPE_F32)
+    pool = torch.full((sc.sc_cache_pool_bytes(*args),), 0xFF, dtype=torch.uint8, device="cuda")
+    cache = sc.sc_cache_create(pool, *args)
+    table = torch.empty(sc.sc_rope_table_bytes(gh, gw, dims, 64), dtype=torch.uint8, device="cuda")
+    rp = sc.sc_rope_table_build(table, gh, gw, dims, 64)
+    k, kv = to_device(normal((n, heads, hd), (7, TAG_K, 5)), sc.SC_DTYPE_F32)
+    cache.append(0, (chunk, 0), k, k, rope=rp)
+    torch.cuda.synchronize()
+    cs = table.view(torch.float32).view(-1, 2).cpu().numpy()
+    ends = np.cumsum([0, 64 * (dims[0] // 2), gh * (dims[1] // 2), gw * (dims[2] // 2)])
+    axes = [cs[a:b].reshape(-1, d // 2, 2) for a, b, d in zip(ends, ends[1:], dims)]
+    tok = np.arange(n)
+    pos = [chunk * frames + tok // tpp, tok % tpp // gw, tok % gw]
+    rot = np.concatenate([ax[p] for ax, p in zip(axes, pos)], 1)[:, None]  # [n, 1, hd / 2, 2]
+    c, s = rot[..., 0], rot[..., 1]
+    x0, x1 = kv[..., 0::2].astype(np.float32), kv[..., 1::2].astype(np.float32)
+    r0 = x0.astype(np.float64) * c - (x1 * s).astype(np.float64)
+    r1 = x0.astype(np.float64) * s + (x1 * c).astype(np.float64)
+    want = np.stack([r0, r1], -1).reshape(n, heads, hd).astype(np.float32)
+    got = pool.view(torch.float32).view(frames, 2, heads, tpp, hd)[:, 0].permute(0, 2, 1, 3).reshape(n, heads, hd)
+    assert np.array_equal(got.cpu().numpy().view(np.int32), want.view(np.int32))
+
+
 @pytest.mark.parametrize("shift", [0, 2], ids=["aligned", "shifted"])
 @pytest.mark.parametrize("k_norm", [False, True])
 @pytest.mark.parametrize("heads,tpp,pages", [(2, 8, 1), (2, 72, 3), (12, 200, 1)])
