@@ -1243,10 +1243,18 @@ __global__ __launch_bounds__(64 * WV_NW, 2) void attn_waves_kernel(const uint16_
     }
     bf16x8 pb[1][2];
     probs<1>(s, pb);
-    if (more)
+    if (more) {
       copies_landed<KC>();  // V(t); K(t + 1) may still be under way
-    else
+    } else {
       copies_landed<0>();
+      if (kv.nk < tn && t0 + 8 * lg >= kv.nk) {
+        // the columns past the node's end hold a real token's values, and an
+        // infinity there would make 0 x inf: each lane clears what it reads
+#pragma unroll
+        for (int db = 0; db < 8; ++db)
+          *reinterpret_cast<u32x4*>(vl + L.voff[0] + db * (16 * 2 * WV_BK)) = u32x4{};
+      }
+    }
     pv_tile<1>(vl, L, pb, oacc);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) lsum[qb] = mfma16(ones, pb[0][qb], lsum[qb]);

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import paper_2609_22283_amd as sc
+from synth import TAG_V, normal
 from synth.configs import Geometry
 
 from gpu_cases import AttnCase, bf16_gates, sample_rows
@@ -59,3 +60,26 @@ def test_attention_forms(name, geo, nodes, rising):
     again = case.run()
     for i in range(nodes):
         assert np.array_equal(out[i], again[i])
+
+
+@pytest.mark.parametrize("geo,nodes", [(_geo(2, 1, 5, 8, 6), 3), (_geo(2, 1, 8, 9, 4), 1), (_geo(2, 1, 8, 9, 6), 2)])
+def test_waves_infinite_values(geo, nodes):
+    """A channel of +inf in every value row stays +inf where a node's keys end
+    inside the waves form's 32-key tile (280, 360 and 504 keys): the masked columns
+    of that tile hold a real token's values at weight zero, and 0 x inf would be
+    NaN.  The other channels stay right."""
+    assert (geo.W + 1) * geo.tokens_per_chunk % 32 != 0
+
+    def value_fn(st):
+        v = normal((geo.tokens_per_chunk, geo.heads, geo.head_dim), (67, TAG_V) + tuple(st))
+        v[:, :, 5] = np.inf
+        return v
+
+    pack = [(geo.W + i, 2) for i in range(nodes)]
+    resident = [(c, 2) for c in range(geo.W)]
+    case = AttnCase(geo, sc.SC_DTYPE_BF16, "same", pack, resident, seed=67, value_fn=value_fn)
+    out = case.run()
+    rest = np.arange(geo.head_dim) != 5
+    for i in range(nodes):
+        assert np.all(out[i][:, :, 5] == np.inf), i
+        bf16_gates(out[i][:, :, rest], case.oracle(i)[:, :, rest], f"node {pack[i]}")
