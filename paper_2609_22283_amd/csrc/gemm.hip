@@ -143,21 +143,25 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
   constexpr int WM = 16 * FB, GWN = 16 * TB;
   const int32_t lg = lane >> 4, c16 = lane & 15;
   // The folded RMSNorm of the input rows: D is linear in the row, so the
-  // token's 1 / rms scales its accumulators before anything else (while
-  // every lane is active: it may come from another lane).
-  if constexpr (EPI != EPI_RESIDUAL) {
-    if (ep.row_scale || ep.row_part) {
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        const float r = pre.factor(tb, c16);
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[fb][tb][e] *= r;
-      }
-    }
-  }
+  // token's 1 / rms scales its accumulators before anything else (taken while
+  // every lane is active: it may come from another lane).  Without one it is 1,
+  // not a branch around the products: with all accumulators updated under a
+  // condition the compiler held them twice, and the 256 x 256 tiles spilled (9
+  // registers with GELU, 24 with STORE: MLP-up of 18720 tokens 487 us, now 473).
+  const auto row_factor = [&](int32_t tb) __attribute__((always_inline)) {
+    float r = 1.f;
+    if (EPI != EPI_RESIDUAL && (ep.row_scale || ep.row_part)) r = pre.factor(tb, c16);
+    return r;
+  };
   if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      const float r = row_factor(tb);
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[fb][tb][e] *= r;
+    }
     // a 256-feature tile lies in one of q, k, v (hidden is a multiple of 256)
     // and each wave's 128 or 64 features in one head (head_dim 128)
     const int32_t part = fw / ep.hidden, sec = part + (ep.w2 ? 1 : 0);
@@ -223,26 +227,21 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
       }
       return;
     }
-    // RoPE pairs p = d / 2 + pp: the axis of each pair (time, height, width)
-    // and its table offset are fixed per lane, so they are resolved once;
-    // per token only the axis's position term is selected (no branches).
+    // RoPE pairs p = d / 2 + pp: the axis of each pair (time, height, width) is
+    // fixed per lane, so it is resolved once; per token only the table row of the
+    // pair's axis is selected (no branches).  The offset of a pair within its row
+    // is p and a constant of the axis, and is not kept: on 256 x 224 tiles
+    // that register a pair was what spilled (18720 tokens 275 us, now 262).
     const bool rope = ep.rope_table != nullptr;  // q or k here
-    int32_t rbase[FB][2], rax[FB][2];
+    int32_t rax[FB][2];
+    const int32_t p0 = dbase / 2, p_h = ep.pairs_t, p_w = ep.pairs_t + ep.pairs_h;
+    const int32_t base_h = (int32_t)ep.rope_off_h - p_h, base_w = (int32_t)ep.rope_off_w - p_w;
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
       for (int pp = 0; pp < 2; ++pp) {
-        const int32_t p = (dbase + 16 * fb) / 2 + pp;
-        if (p < ep.pairs_t) {
-          rax[fb][pp] = 0;
-          rbase[fb][pp] = p;
-        } else if (p < ep.pairs_t + ep.pairs_h) {
-          rax[fb][pp] = 1;
-          rbase[fb][pp] = (int32_t)ep.rope_off_h + (p - ep.pairs_t);
-        } else {
-          rax[fb][pp] = 2;
-          rbase[fb][pp] = (int32_t)ep.rope_off_w + (p - ep.pairs_t - ep.pairs_h);
-        }
+        const int32_t p = p0 + 8 * fb + pp;
+        rax[fb][pp] = p < p_h ? 0 : p < p_w ? 1 : 2;
       }
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
@@ -252,7 +251,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
       const int32_t frame = (int32_t)fast_div((uint32_t)tok, ep.tpp_div), n = tok - frame * ep.tpp;
       const int32_t pos_t = ep.node_chunk[node] * ep.ppc + frame;
       const int32_t pos_h = (int32_t)fast_div((uint32_t)n, ep.gw_div), pos_w = n - pos_h * ep.grid_w;
-      const int32_t term_t = pos_t * ep.pairs_t, term_h = pos_h * ep.pairs_h, term_w = pos_w * ep.pairs_w;
+      const int32_t row_t = pos_t * ep.pairs_t, row_h = base_h + pos_h * ep.pairs_h, row_w = base_w + pos_w * ep.pairs_w;
       char* slot_base = ep.layer_base + (size_t)ep.node_slot[node * ep.ppc + frame] * ep.slot_bytes;
       uint16_t* qrow = ep.q_out + (size_t)t * ep.hidden + hf0 + 4 * lg;
       uint16_t* krow = reinterpret_cast<uint16_t*>(slot_base) + ((size_t)head * ep.tpp + n) * ep.head_dim;
@@ -265,8 +264,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
 #pragma unroll
           for (int pp = 0; pp < 2; ++pp) {
             const int32_t ax = rax[fb][pp];
-            const int32_t idx = rbase[fb][pp] + (ax == 0 ? term_t : ax == 1 ? term_h : term_w);
-            const float2 cs = ep.rope_table[idx];
+            const float2 cs = ep.rope_table[p0 + 8 * fb + pp + (ax == 0 ? row_t : ax == 1 ? row_h : row_w)];
             float& x0 = pp ? v2 : v0;
             float& x1 = pp ? v3 : v1;
             const float r0 = x0 * cs.x - x1 * cs.y, r1 = x0 * cs.y + x1 * cs.x;
@@ -284,13 +282,12 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
       }
     }
   } else {
-    if (EPI == EPI_STORE && ep.ss_part)
-      store_sum_squares(acc, ep.ss_part, ep.n_part, (fw) / kSsPartWidth, tw, T, lg, c16);
     constexpr int FPG = kSsPartWidth / 16;  // 16-feature blocks per sum-of-squares partial
     static_assert(FB % FPG == 0, "whole partials per wave");
-    const bool row_sums = EPI == EPI_RESIDUAL && ep.ss_part;
+    const bool row_sums = (EPI == EPI_RESIDUAL || EPI == EPI_STORE) && ep.ss_part;
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
+      const float rf = row_factor(tb);
       const int32_t t = tw + 16 * tb + c16;
       if (t >= T) continue;  // uniform over the 4 lanes of a token, so the butterflies below stay inside it
       uint16_t* orow = ep.out + (size_t)t * ep.ld_out + fw + 4 * lg;
@@ -305,7 +302,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
       for (int fb = 0; fb < FB; ++fb) {
           float v[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[fb][tb][e];
+          for (int e = 0; e < 4; ++e) v[e] = EPI == EPI_RESIDUAL ? acc[fb][tb][e] : acc[fb][tb][e] * rf;
           uint16_t* dst = orow + 16 * fb;
           if constexpr (EPI == EPI_RESIDUAL) {
             if (gate) {
@@ -325,12 +322,15 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
           } else if constexpr (EPI == EPI_GELU) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+          } else if (row_sums) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ssq[fb / FPG] = fmaf(v[e], v[e], ssq[fb / FPG]);
           }
           u32x2 pk;
           pk.x = pack_bf16x2(v[0], v[1]);
           pk.y = pack_bf16x2(v[2], v[3]);
           *reinterpret_cast<u32x2*>(dst) = pk;
-          if (row_sums) {  // of the values as stored
+          if (EPI == EPI_RESIDUAL && row_sums) {  // of the values as stored
             const float a = __uint_as_float(pk.x << 16), b = __uint_as_float(pk.x & 0xffff0000u);
             const float c = __uint_as_float(pk.y << 16), d = __uint_as_float(pk.y & 0xffff0000u);
             ssq[fb / FPG] = fmaf(a, a, fmaf(b, b, fmaf(c, c, fmaf(d, d, ssq[fb / FPG]))));
@@ -654,8 +654,9 @@ constexpr TileCost kTiles[] = {
     {128, 64, 2 * kCUs, 0.48, 6.5, 0.262, 5.0, 0.0},   {64, 64, kCUs, 0.184, 0.6, 0.184, 0.6, 3.5},
 };
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
-// Tile256's 128 x 64 wave tiles spill with these epilogues' state (104 and 96
-// registers; QKV 18720 tokens 331 us against 272 on Tile224): not built.
+// Not for QKV and RESIDUAL: their epilogues' state beside Tile256's 128 x 64 wave
+// tiles spills about a hundred registers (QKV of 18720 tokens 331 us, 262 on
+// Tile224).  No tile that is built spills.
 constexpr bool tile256_built(int epi) { return epi == EPI_GELU || epi == EPI_STORE; }
 
 // The tile and the number of parts of the contraction of a launch: the
