@@ -96,9 +96,10 @@ __device__ __forceinline__ float token_factor(const GemmEpilogue& ep, int32_t Kd
 // RESIDUAL: the residual stream's out[t][f], loaded before the loop so that it
 // lands during it (after the loop, every CU of the launch would read its residual
 // tile at once).  Rows past T read the last row (valid memory, values unused).
-// (On the widest tiles, above kEarlyResidual blocks of a wave: read in the
-// epilogue, since the registers would spill; out-projection at 18720 tokens
-// on Tile224 90 us, 93 us with the early read.)
+// (At most kEarlyResidual blocks of a wave: on the widest tiles not the last token
+// blocks, since the registers would spill.  In the block at 18720 tokens on
+// Tile224, with 0, 8, 16, 20 and 24 of the wave's 28 blocks read early:
+// out-projection 114, 111, 108.5, 107, 106 us, MLP-down 441 .. 434.)
 // The others: the folded RMSNorm's per-token factors, fetched after the first
 // stages' copies are on their way.  Where several waves share tokens (SHARED),
 // the work-group's first threads fetch one each into LDS; else lane j takes
@@ -106,17 +107,17 @@ __device__ __forceinline__ float token_factor(const GemmEpilogue& ep, int32_t Kd
 constexpr int kEarlyResidual = 24;
 template <int EPI, int FB, int TB, bool SHARED>
 struct EpiPre {
-  static constexpr bool RES = EPI == EPI_RESIDUAL && FB * TB <= kEarlyResidual;
+  static constexpr int RTB = EPI != EPI_RESIDUAL ? 0 : FB * TB <= kEarlyResidual ? TB : kEarlyResidual / FB;  // token blocks
   static_assert(SHARED || EPI == EPI_RESIDUAL || TB <= 4, "a factor per lane");
-  u32x2 res[RES ? TB : 1][RES ? FB : 1];
+  u32x2 res[RTB ? RTB : 1][FB];
   float rtok;         // this lane's token's
   const float* rows;  // SHARED: those of the wave's tokens
   __device__ __forceinline__ void load_residual(const GemmEpilogue& ep, int32_t T, int32_t fw, int32_t tw,
                                                 int32_t lane) {
-    if constexpr (RES) {
+    if constexpr (RTB > 0) {
       const int32_t lg = lane >> 4, c16 = lane & 15;
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
+      for (int tb = 0; tb < RTB; ++tb) {
         const int32_t t = min(tw + 16 * tb + c16, T - 1);
         const uint16_t* orow = ep.out + (size_t)t * ep.ld_out + fw + 4 * lg;
 #pragma unroll
@@ -311,7 +312,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
               for (int e = 0; e < 4; ++e) v[e] *= gv[e];
             }
             u32x2 r;
-            if constexpr (EpiPre<EPI, FB, TB, SHARED>::RES)
+            if (tb < EpiPre<EPI, FB, TB, SHARED>::RTB)  // known when unrolled
               r = pre.res[tb][fb];
             else
               r = *reinterpret_cast<const u32x2*>(dst);
