@@ -32,6 +32,26 @@ extern "C" {
 int sc_timer_enable(int on);
 int sc_timer_read(const char* kind, int32_t* launches, double* total_ms);
 
+/* ---- Kernel forms (measurement support) ----------------------------------
+ * Which form of a kernel a call would launch (nothing is launched), so that a
+ * test or a benchmark can say which one it covers.
+ * sc_attention_form: sc_attention with the plan's workspace.  *queries:
+ * query rows per work-group (bf16: 32 with a node's keys split over the waves,
+ * 64, 128 or 256 with a unit's keys in order; fp32: 16); *ring: K/V tiles in
+ * the LDS ring of a unit form, else 1; *pieces: key-range pieces that each
+ * unit of the last round is cut into (1: none).
+ * sc_gemm_form: the projection of the given timer kind ("gemm_qkv", "gemm_out",
+ * "gemm_up", "gemm_down", "gemm_cross_q", "gemm_cross_out", "gemm_condition")
+ * at n_features x n_tokens outputs over k, in a block or a condition call.
+ * *tile_features, *tile_tokens: output tile per work-group; *ring: 64-k stages
+ * in its LDS ring; *parts: work-groups that share a tile's contraction.
+ * Errors: SC_EINVAL (null pointer, plan of another cache or without nodes,
+ * unknown kind), SC_EUNSUPPORTED (shapes that the call refuses). */
+int sc_attention_form(const sc_plan* plan, const sc_cache* cache, int32_t* queries, int32_t* ring,
+                      int32_t* pieces);
+int sc_gemm_form(const char* kind, int32_t n_features, int32_t n_tokens, int32_t k,
+                 int32_t* tile_features, int32_t* tile_tokens, int32_t* ring, int32_t* parts);
+
 /* ---- Matrix-core ceiling probe (measurement support) ------------------
  * Launches one kernel on `stream` that issues only 16x16x32 bf16 MFMAs from
  * registers (two 8-wave work-groups per CU, `iters` rounds of 16 MFMAs per

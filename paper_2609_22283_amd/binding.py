@@ -20,6 +20,7 @@ __all__ = [
     "sc_abi_version", "sc_selection_build", "sc_cache_pool_bytes", "sc_cache_create",
     "sc_rope_table_bytes", "sc_rope_table_build", "sc_plan_build", "sc_attention",
     "sc_attention_workspace_bytes", "sc_block_workspace_bytes", "sc_block_forward", "sc_sampler_step",
+    "sc_attention_form", "sc_gemm_form",
     "sc_timer_enable", "sc_timer_read", "sc_probe_mfma_out_bytes", "sc_probe_mfma", "sc_probe_read",
     "Selection", "Cache", "Plan", "Rope", "BlockWeights", "CrossAttn",
     "sc_plan_condition", "sc_condition_workspace_bytes", "sc_condition_append",
@@ -45,6 +46,7 @@ EXPORTED_SYMBOLS = [
     "sc_condition_workspace_bytes", "sc_condition_append",
     "sc_attention_workspace_bytes", "sc_attention",
     "sc_block_workspace_bytes", "sc_block_forward", "sc_sampler_step",
+    "sc_attention_form", "sc_gemm_form",
     "sc_timer_enable", "sc_timer_read", "sc_probe_mfma_out_bytes", "sc_probe_mfma", "sc_probe_read",
     "sc_pipeline_rounds", "sc_pipeline_round_nodes", "sc_cache_release_unread", "sc_stack_forward",
     "sc_serial_steps", "sc_serial_step_node", "sc_block_workspace_views",
@@ -149,6 +151,8 @@ _SIG = {
                                   _P, _P, _P, C.c_int64, _P]),
     "sc_timer_enable": (C.c_int, [C.c_int]),
     "sc_timer_read": (C.c_int, [C.c_char_p, _I32P, C.POINTER(C.c_double)]),
+    "sc_attention_form": (C.c_int, [_P, _P, _I32P, _I32P, _I32P]),
+    "sc_gemm_form": (C.c_int, [C.c_char_p, C.c_int32, C.c_int32, C.c_int32, _I32P, _I32P, _I32P, _I32P]),
     "sc_probe_mfma_out_bytes": (C.c_size_t, []),
     "sc_probe_mfma": (C.c_int, [C.c_int32, C.c_int32, _P, C.c_size_t, C.POINTER(C.c_double), _P]),
     "sc_probe_read": (C.c_int, [_P, C.c_size_t, _P, _P]),
@@ -496,6 +500,20 @@ def sc_timer_read(kind: str):
     n, ms = C.c_int32(), C.c_double()
     _check(lib.sc_timer_read(kind.encode(), C.byref(n), C.byref(ms)))
     return n.value, ms.value
+
+
+def sc_attention_form(plan: "Plan", cache: "Cache") -> Tuple[int, int, int]:
+    """(queries per work-group, ring depth, pieces per tail unit) sc_attention would launch."""
+    v = [C.c_int32() for _ in range(3)]
+    _check(lib.sc_attention_form(plan.handle, cache.handle, *[C.byref(a) for a in v]))
+    return tuple(a.value for a in v)
+
+
+def sc_gemm_form(kind: str, n_features: int, n_tokens: int, k: int) -> Tuple[int, int, int, int]:
+    """(tile features, tile tokens, ring depth, parts of the contraction) of a projection's launch."""
+    v = [C.c_int32() for _ in range(4)]
+    _check(lib.sc_gemm_form(kind.encode(), n_features, n_tokens, k, *[C.byref(a) for a in v]))
+    return tuple(a.value for a in v)
 
 
 def sc_probe_mfma_out_bytes() -> int:

@@ -1662,6 +1662,28 @@ int launch_attention(const sc_plan* p, const sc_cache* c, int32_t layer, const v
   return launch_scheduled(p, c, layer, q, o, scale, ws, attn_schedule(p, c, need), stream);
 }
 
+}  // namespace sc
+
+extern "C" int sc_attention_form(const sc_plan* p, const sc_cache* c, int32_t* queries, int32_t* ring,
+                                 int32_t* pieces) {
+  using namespace sc;
+  if (!p || !c || !queries || !ring || !pieces) return fail(SC_EINVAL, "null argument");
+  if (p->cache != c) return fail(SC_EINVAL, "plan was built for another cache");
+  if (p->nodes.empty()) return fail(SC_EINVAL, "a plan without nodes launches nothing");
+  const int rc = attention_check(p, c);
+  if (rc != SC_OK) return rc;
+  *queries = F32_BQ;
+  *ring = *pieces = 1;
+  if (c->d.dtype == SC_DTYPE_F32) return SC_OK;
+  const AttnSchedule ts = attn_schedule(p, c, attention_workspace_bytes(p, c));
+  *queries = ts.sh.bq;
+  *ring = ts.sh.ring;
+  *pieces = ts.split;
+  return SC_OK;
+}
+
+namespace sc {
+
 // ------------------------------------------------ attention without allocation
 // The split-key partials of sc_attention_noalloc live in this library-owned
 // array; every GPU the library runs on holds its own copy until the process

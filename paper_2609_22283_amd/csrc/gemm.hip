@@ -645,7 +645,8 @@ using Tile64 = GemmTile<64, 64, 1, 2, 2, 5, 2>;         // two per CU
 // (first copies, epilogue), a lone one on a CU that could hold two
 // `stage1`, `fixed1`; `once` is paid once per launch.
 struct TileCost {
-  int bm, bn, slots;  // work-groups resident at once
+  int bm, bn;
+  int slots;  // work-groups of a round: those resident at once (64 x 64: one per CU, since two there take turns)
   double stage, fixed, stage1, fixed1, once;
 };
 constexpr TileCost kTiles[] = {
@@ -655,6 +656,8 @@ constexpr TileCost kTiles[] = {
     {128, 64, 2 * kCUs, 0.48, 6.5, 0.262, 5.0, 0.0},   {64, 64, kCUs, 0.184, 0.6, 0.184, 0.6, 3.5},
 };
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kTileRings[kTileCount] = {Tile256::D, Tile224::D, Tile192::D, Tile256x128::D,
+                                        Tile128::D, Tile128Deep::D, Tile128x64::D, Tile64::D};
 // Not for QKV and RESIDUAL: their epilogues' state beside Tile256's 128 x 64 wave
 // tiles spills about a hundred registers (QKV of 18720 tokens 331 us, 262 on
 // Tile224).  No tile that is built spills.
@@ -760,6 +763,37 @@ int launch_gemm(int epi, int timer_kind, const uint16_t* W, const uint16_t* X, i
   SC_HIP(hipGetLastError());
   return SC_OK;
 }
+
+}  // namespace sc
+
+extern "C" int sc_gemm_form(const char* kind, int32_t n_features, int32_t n_tokens, int32_t k,
+                            int32_t* tile_features, int32_t* tile_tokens, int32_t* ring, int32_t* parts) {
+  using namespace sc;
+  if (!kind || !tile_features || !tile_tokens || !ring || !parts) return fail(SC_EINVAL, "null argument");
+  static const struct {
+    const char* name;
+    int epi;
+    bool scratch;
+  } kinds[] = {{"gemm_qkv", EPI_QKV, true},       {"gemm_out", EPI_RESIDUAL, true},
+               {"gemm_up", EPI_GELU, true},       {"gemm_down", EPI_RESIDUAL, true},
+               {"gemm_cross_q", EPI_STORE, true}, {"gemm_cross_out", EPI_RESIDUAL, true},
+               {"gemm_condition", EPI_QKV, false}};
+  for (const auto& e : kinds) {
+    if (std::strcmp(kind, e.name) != 0) continue;
+    if (n_features <= 0 || n_features % GBM || k <= 0 || k % GBK || n_tokens <= 0)
+      return fail(SC_EUNSUPPORTED, "gemm needs F %% %d == 0, K %% %d == 0 (F=%d K=%d T=%d)", GBM, GBK, n_features, k,
+                  n_tokens);
+    const GemmShape g = gemm_shape(e.epi, n_features, n_tokens, k, e.scratch ? attention_workspace_bound() : 0);
+    *tile_features = kTiles[g.tile].bm;
+    *tile_tokens = kTiles[g.tile].bn;
+    *ring = kTileRings[g.tile];
+    *parts = g.split;
+    return SC_OK;
+  }
+  return fail(SC_EINVAL, "unknown projection '%s'", kind);
+}
+
+namespace sc {
 
 // ------------------------------------------------------------------ RMSNorm
 // y = x / sqrt(mean(x^2) + eps), one wave per row, fp32 math, bf16 in/out;

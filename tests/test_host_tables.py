@@ -217,6 +217,47 @@ def test_attention_workspace_size():
     assert sc.sc_attention_workspace_bytes(plan, f32) == 0
 
 
+def test_kernel_forms_stay_within_their_scratch():
+    """The forms that a call would launch, over random shapes: the partials of an
+    attention's pieces fit the workspace that the plan asks for, those of a
+    projection's parts the block's scratch (1024 partial results of 256 rows), and
+    a part never has less than one 64-k stage.  What the calls refuse is refused."""
+    rnd = random.Random(11)
+    per_cu = {(64, 4): 2, (64, 3): 3, (128, 2): 2, (256, 2): 1}
+    seen = set()
+    for _ in range(300):
+        heads, ppc, tpp = rnd.choice([1, 2, 7, 12]), rnd.randint(1, 3), 8 * rnd.randint(8, 100)
+        n, W = rnd.randint(1, 6), rnd.randint(0, 20)
+        if rnd.random() < 0.25:
+            ppc, tpp, W = 1, 8 * rnd.randint(4, 8), rnd.randint(0, 4)   # short nodes
+        cache = sc.sc_cache_create(0x100000, 1, heads, 128, tpp, ppc, (n + W) * ppc)
+        sc.sc_plan_build(sc.sc_selection_build("clean", 4, 0, [(c, 2) for c in range(W)] or [(0, 2)]), cache)
+        plan = sc.sc_plan_build(sc.sc_selection_build("same", 4, W, [(W + i, 2) for i in range(n)]), cache)
+        bq, ring, pieces = sc.sc_attention_form(plan, cache)
+        seen.add((bq, pieces > 1))
+        if pieces > 1:
+            units = n * heads * -(-ppc * tpp // bq)
+            tail = units % (256 * per_cu[bq, ring])
+            assert 0 < tail * pieces * bq * 130 * 4 <= sc.sc_attention_workspace_bytes(plan, cache)
+    assert {(32, False), (64, False), (128, False), (256, False), (128, True), (256, True)} <= seen
+    for _ in range(300):
+        f, k, t = 256 * rnd.randint(1, 48), 64 * rnd.randint(1, 160), rnd.randint(1, 4000)
+        bm, bn, ring, parts = sc.sc_gemm_form(rnd.choice(["gemm_qkv", "gemm_out", "gemm_up", "gemm_cross_q"]), f, t, k)
+        assert f % bm == 0 and ring >= 2 and 1 <= parts <= k // 64
+        assert parts == 1 or 4 * parts * f * (-(-t // 16) * 16) <= 1024 * 256 * 130 * 4
+        assert sc.sc_gemm_form("gemm_condition", f, t, k)[3] == 1   # no scratch there
+    f32 = sc.sc_cache_create(0x100000, 1, 2, 64, 16, 1, 8, sc.SC_DTYPE_F32)
+    plan = sc.sc_plan_build(sc.sc_selection_build("clean", 4, 0, [(0, 0)]), f32)
+    assert sc.sc_attention_form(plan, f32) == (16, 1, 1)
+    for call, code in [(lambda: sc.sc_attention_form(plan, cache), sc.SC_EINVAL),
+                       (lambda: sc.sc_gemm_form("gemm_sideways", 256, 8, 64), sc.SC_EINVAL),
+                       (lambda: sc.sc_gemm_form("gemm_up", 300, 8, 64), sc.SC_EUNSUPPORTED),
+                       (lambda: sc.sc_gemm_form("gemm_up", 256, 0, 64), sc.SC_EUNSUPPORTED)]:
+        with pytest.raises(sc.ScError) as e:
+            call()
+        assert e.value.code == code
+
+
 def test_empty_pack_is_a_no_op():
     """An empty pack selects nothing, plans nothing and launches nothing."""
     sel = sc.sc_selection_build("prog", 4, 6, [])
