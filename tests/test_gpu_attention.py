@@ -1,10 +1,9 @@
 """GPU parity of the packed paged attention against the CPU oracle.
 
 Covers the tiny fp32 case (every node of 4 chunks x 5 levels under all three
-policies, several pack shapes), small bf16 packs on each work-group shape
-(256, 128 and 64 queries) whose pages (104, 96 and 40 tokens) leave ragged
-tails inside key tiles, the short-context streaming shape and long windows
-cut into key-range pieces, the Wan-shaped clean / same-level /
+policies, several pack shapes), small bf16 packs whose pages (104, 96 and 40
+tokens) leave ragged tails inside key tiles, the short-context streaming shape
+and long windows cut into key-range pieces, the Wan-shaped clean / same-level /
 progressive packs on sampled rows, the segment probe, negative controls
 (mistakes planted in the oracle must fail the gates), NaN poisoning of
 unused slots, packed vs sequential, run-to-run determinism and the workspace
@@ -72,7 +71,8 @@ def test_small_bf16_packs(kind, pack, resident):
 
 @pytest.mark.parametrize("kind,pack,resident", SMALL_PACKS)
 def test_short_bf16_packs(kind, pack, resident):
-    """Nodes of 96 queries run on the 128-query (4-wave) work-group shape."""
+    """Nodes of 96 queries over up to seven 96-token pages: their keys over the
+    waves of a work-group, or (96 keys) one 128-query unit."""
     case = AttnCase(SHORT, sc.SC_DTYPE_BF16, kind, pack, resident, seed=6)
     out = case.run()
     for i in range(len(pack)):
@@ -81,7 +81,8 @@ def test_short_bf16_packs(kind, pack, resident):
 
 @pytest.mark.parametrize("kind,pack,resident", SMALL_PACKS)
 def test_narrow_bf16_packs(kind, pack, resident):
-    """Nodes of 40 queries run on the 64-query (2-wave, 32-key tile) shape."""
+    """Nodes of 40 queries over up to seven 40-token pages: their keys over the
+    waves of a work-group, or (up to 120 keys) 64-query units."""
     case = AttnCase(NARROW, sc.SC_DTYPE_BF16, kind, pack, resident, seed=12)
     out = case.run()
     for i in range(len(pack)):
@@ -97,6 +98,7 @@ def test_narrow_long_windows_cut_into_pieces():
     pack = [(41 * i + W, 4) for i in range(3)]
     resident = [(41 * i + r, 0) for i in range(3) for r in range(W)]
     case = AttnCase(geo, sc.SC_DTYPE_BF16, "clean", pack, resident, seed=13)
+    assert sc.sc_attention_form(case.plan, case.cache) == (64, 4, 11)
     out = case.run()
     assert case.workspace_bytes > 0
     for i in range(len(pack)):
@@ -113,6 +115,7 @@ def test_narrow_many_units(heads):
     pack = [(3 * i + 2, 4) for i in range(64)]
     resident = [(3 * i + r, 0) for i in range(64) for r in range(2)]
     case = AttnCase(geo, sc.SC_DTYPE_BF16, "clean", pack, resident, seed=14)
+    assert sc.sc_attention_form(case.plan, case.cache) == (64, 3, 1)
     out = case.run()
     assert case.workspace_bytes == 0
     for i in (0, 21, 42, 63):
@@ -128,6 +131,7 @@ def test_wide_long_windows_cut_into_pieces():
     pack = [(41 * i + W, 4) for i in range(3)]
     resident = [(41 * i + r, 0) for i in range(3) for r in range(W)]
     case = AttnCase(geo, sc.SC_DTYPE_BF16, "clean", pack, resident, seed=15)
+    assert sc.sc_attention_form(case.plan, case.cache) == (128, 2, 7)
     out = case.run()
     assert case.workspace_bytes > 0
     for i in range(len(pack)):
@@ -264,15 +268,14 @@ def test_negative_controls_fail_gates():
             bf16_gates(out[node], want, name)
 
 
-@pytest.mark.parametrize("geo", [SMALL, SHORT, NARROW], ids=["256-query", "128-query", "64-query"])
+@pytest.mark.parametrize("geo", [SMALL, SHORT, NARROW], ids=["312-queries", "96-queries", "40-queries"])
 def test_logits_far_above_first_tile(geo):
-    """K channel 0 is 0 on each node's first page and 600 on most later
-    pages (first page of every state for three-frame chunks; chunks 0..3,
-    the first pages of this pack's nodes, for one-frame chunks), with Q
-    channel 0 = 1: later logits sit about 76 (log2 units) above the maximum
-    of a node's first key tile, past the kernel's 2^64 guard on probability
-    sums, so the work items redo their keys in two exact passes.  The
-    softmax is still the plain one: compared with the oracle."""
+    """K channel 0 is 0 on some pages (the first of every state for three-frame
+    chunks; chunks 0..3 for one-frame chunks) and 600 on the others, with Q
+    channel 0 = 1: logits about 76 (log2 units) apart within a node, whichever
+    page its kernel starts at.  The softmax is still the plain one: compared
+    with the oracle.  (test_gpu_attention_forms.py takes each form of the kernel
+    past its guard on the first tile's maximum.)"""
     kind, pack, resident = SMALL_PACKS[0]
     tpp = geo.tokens_per_page
 

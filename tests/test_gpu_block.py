@@ -223,8 +223,8 @@ def test_small_block_level_modulation(kind, pack, resident):
 
 
 def test_short_block_prog():
-    """A progressive pack of one-frame, 96-token chunks (the attention's
-    128-query work-group shape inside the block)."""
+    """A progressive pack of one-frame, 96-token chunks (the attention with a
+    node's keys over the waves, inside the block)."""
     pack = [(6, 0), (7, 1), (8, 2), (9, 3), (10, 4)]
     case = BlockCase(SHORT, "prog", pack, [(c, 0) for c in range(6)], seed=13)
     got = case.run()
@@ -409,11 +409,14 @@ def test_wan_block_attention_branch():
 
 def test_wan_width_block_1800_tokens():
     """Wan widths (hidden 1536, 12 heads, MLP 8960) over one 1800-token chunk
-    (one 15 x 120 frame) with one resident state: the MLP-up GEMM runs on
-    192-token tiles here (350 tiles, 2 rounds at 0.75 of a tile, against 280
-    tiles in 2 full rounds at 256), as do the QKV GEMM, and the out/down GEMMs
-    on 128-token tiles."""
+    (one 15 x 120 frame) with one resident state: QKV and MLP-up run on 256 x
+    192 tiles that end inside the chunk, the out-projection on 128 x 128 ones, and
+    MLP-down on 256 x 192 in four parts."""
     import dataclasses
+    assert sc.sc_gemm_form("gemm_qkv", 4608, 1800, 1536) == (256, 192, 2, 1)
+    assert sc.sc_gemm_form("gemm_up", 8960, 1800, 1536) == (256, 192, 2, 1)
+    assert sc.sc_gemm_form("gemm_out", 1536, 1800, 1536) == (128, 128, 4, 1)
+    assert sc.sc_gemm_form("gemm_down", 1536, 1800, 8960) == (256, 192, 2, 4)
     geo = dataclasses.replace(WAN, grid_h=15, grid_w=120, frames_per_chunk=1)
     case = BlockCase(geo, "clean", [(1, 4)], [(0, 0)], seed=17)
     got = case.run()

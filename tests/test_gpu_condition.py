@@ -53,7 +53,7 @@ def test_condition_append_matches_oracle(k_norm):
 
 
 @pytest.mark.parametrize("nq,L,pages", [(300, 200, 1), (96, 200, 1), (300, 256, 2)],
-                         ids=["256-query", "128-query", "two-page-condition"])
+                         ids=["300-queries", "96-queries", "two-page-condition"])
 def test_attention_over_condition_plan(nq, L, pages):
     """Each pack node reads its own condition (two nodes share one), every
     query sees all L tokens; ragged L and ragged query counts; a condition
@@ -118,8 +118,8 @@ def test_small_block_qk_norm_and_cross(variant):
 
 
 def test_short_block_qk_norm_and_cross():
-    """One-frame 96-token chunks: the 128-query attention shape for both the
-    pack and the condition."""
+    """One-frame 96-token chunks, and a 72-token condition: short nodes for both
+    attentions."""
     qk = np.stack([gains(SHORT.hidden, (35, TAG_GAIN, s)) for s in range(2)])
     cross = ConditionCase(SHORT, 72, seed=36, q_norm=True, k_norm=True)
     case = BlockCase(SHORT, "prog", PACK, RESIDENT, seed=37, qk=qk, cross=cross)
@@ -145,10 +145,9 @@ def test_wan_block_qk_norm_and_cross_sampled_rows():
 
 def test_wan_width_qk_norm_256_token_tiles():
     """Wan widths with qk-norm over one 3584-token chunk (one 28 x 128
-    frame): the QKV GEMM that also emits the sums of squares runs on
-    256-token tiles here (252 tiles, one round), whose v tile is staged
-    through LDS in two passes.  Sampled output rows, and the whole cached
-    K (normalised) and V pages, against the oracle."""
+    frame), whose MLP-up takes whole 256 x 256 tiles and whose MLP-down is
+    split in two.  Sampled output rows, and the whole cached K (normalised) and
+    V pages, against the oracle."""
     import dataclasses
     geo = dataclasses.replace(WAN, grid_h=28, grid_w=128, frames_per_chunk=1)
     qk = np.stack([gains(WAN.hidden, (44, TAG_GAIN, s)) for s in range(2)])
@@ -160,3 +159,25 @@ def test_wan_width_qk_norm_256_token_tiles():
     k_got, v_got = read_pages(case.pool, geo, case.n_slots, case.cache.slots((1, 4)))
     block_gate(k_got, new_kv[0][0], "3584-token cached K (qk-norm)")
     bf16_gates(v_got, new_kv[0][1], "3584-token cached V")
+
+
+@pytest.mark.parametrize("q_norm", [False, True], ids=["plain", "q_norm"])
+def test_wan_width_cross_32_tokens(q_norm):
+    """Wan widths, one chunk of 32 tokens and a 64-token condition: the
+    contractions of QKV, the condition query (whose reduce kernel makes the
+    RMSNorm's factors from the rows' stored sums), both out-projections and
+    MLP-down are split.  Every row against the oracle."""
+    import dataclasses
+    geo = dataclasses.replace(WAN, grid_h=4, grid_w=8, frames_per_chunk=1)
+    D, M = geo.hidden, geo.mlp
+    for kind, f, k in [("gemm_qkv", 3 * D, D), ("gemm_cross_q", D, D), ("gemm_out", D, D),
+                       ("gemm_cross_out", D, D), ("gemm_down", D, M)]:
+        assert sc.sc_gemm_form(kind, f, 32, k)[3] > 1
+    cross = ConditionCase(geo, 64, seed=46, q_norm=q_norm, k_norm=q_norm)
+    case = BlockCase(geo, "clean", [(1, 4)], [(0, 0)], seed=47, cross=cross)
+    got = case.run()
+    want, new_kv = case.oracle()
+    block_gate(got[0], want[0], "wan-width 32-token cross node (1, 4)", ROUNDINGS["cross_norm" if q_norm else "cross"])
+    k_got, v_got = read_pages(case.pool, geo, case.n_slots, case.cache.slots((1, 4)))
+    bf16_gates(k_got, new_kv[0][0], "32-token cached K")
+    bf16_gates(v_got, new_kv[0][1], "32-token cached V")

@@ -2,7 +2,7 @@
 
 launch_gemm picks one of eight tile shapes and a split of the contraction by
 size; the packs below (window 0: every node attends to itself) make the four
-projections take each of them, with token counts that end inside a tile and
+projections take each of them, which every case asserts, with token counts that end inside a tile and
 inside a 16-token block, and contractions whose parts differ by a stage.  The
 expected block is plain torch in 64 bits on the same bf16 inputs.
 
@@ -30,17 +30,20 @@ from gpu_cases import to_device, torch_mod
 pytestmark = pytest.mark.gpu
 DIMS, EPS = (44, 42, 42), 1e-6
 
-# heads, mlp, nodes, frames, grid_h, grid_w          tiles (rows x tokens, /parts) of QKV, out, up, down
-SIZES = [
-    (12, 8960, 1, 1, 4, 8),     # 32 tokens:     128x64/6, 64x64/8, 64x64, 64x64/10
-    (12, 8960, 1, 1, 8, 9),     # 72 tokens:     64x64, 64x64, 128x64, 128x64/10
-    (12, 8960, 2, 1, 8, 13),    # 208 tokens:    128x64, 64x64, 128x128 deep, 128x128 deep/10
-    (12, 8960, 1, 2, 11, 24),   # 528 tokens:    128x128 deep, 64x64, 256x128, 128x128 deep/4
-    (12, 8960, 1, 1, 25, 40),   # 1000 tokens:   128x128, 128x64, 256x192, 256x128/5
-    (12, 8960, 1, 3, 25, 40),   # 3000 tokens:   256x224, 256x128, 256x224, 256x224/3
-    (12, 8960, 4, 3, 29, 40),   # 13920 tokens:  128x128, 256x192, 256x256, 256x192
-    (6, 3072, 1, 1, 8, 17),     # 136 tokens:    128x64, 64x64, 64x64, 64x64/7
-]
+# (tile features, tile tokens, ring)
+T64, T128X64, T128, T128D = (64, 64, 5), (128, 64, 3), (128, 128, 2), (128, 128, 4)
+T256X128, T192, T224, T256 = (256, 128, 3), (256, 192, 2), (256, 224, 2), (256, 256, 2)
+# heads, mlp, nodes, frames, grid_h, grid_w: the tile and parts of QKV, out, up, down
+SIZES = {
+    (12, 8960, 1, 1, 4, 8): [(T128X64, 6), (T64, 8), (T64, 1), (T64, 10)],             # 32 tokens
+    (12, 8960, 1, 1, 8, 9): [(T64, 1), (T64, 1), (T128X64, 1), (T128X64, 10)],         # 72
+    (12, 8960, 2, 1, 8, 13): [(T128X64, 1), (T64, 1), (T128D, 1), (T128D, 10)],        # 208
+    (12, 8960, 1, 2, 11, 24): [(T128D, 1), (T64, 1), (T256X128, 1), (T128D, 4)],       # 528
+    (12, 8960, 1, 1, 25, 40): [(T128, 1), (T128X64, 1), (T192, 1), (T256X128, 5)],     # 1000
+    (12, 8960, 1, 3, 25, 40): [(T224, 1), (T256X128, 1), (T224, 1), (T224, 3)],        # 3000
+    (12, 8960, 4, 3, 29, 40): [(T128, 1), (T192, 1), (T256, 1), (T192, 1)],            # 13920
+    (6, 3072, 1, 1, 8, 17): [(T128X64, 1), (T64, 1), (T64, 1), (T64, 7)],              # 136
+}
 
 
 def _rms(x):
@@ -54,6 +57,9 @@ def test_block_over_gemm_tiles(size, full):
     heads, mlp, n_nodes, frames, gh, gw = size
     hd, tpp, n = 128, gh * gw, frames * gh * gw
     D, T = heads * 128, n_nodes * frames * gh * gw
+    for (tile, parts), (kind, f, k) in zip(SIZES[size], [("gemm_qkv", 3 * D, D), ("gemm_out", D, D),
+                                                         ("gemm_up", mlp, D), ("gemm_down", D, mlp)]):
+        assert sc.sc_gemm_form(kind, f, T, k) == tile + (parts,)
     nodes = [(i, i) for i in range(n_nodes)]
     gen = lambda shape, tag, s: to_device(normal_parallel(shape, (91, tag), s), sc.SC_DTYPE_BF16)[0]
     w = {"w_qkv": gen((3 * D, D), TAG_W_QKV, 0.02), "w_o": gen((D, D), TAG_W_O, 0.02),
