@@ -367,11 +367,15 @@ int sc_cache_release_unread(sc_cache* cache, const sc_policy* policy, const sc_n
                             int32_t n_future);
 
 /* The network F_theta of Eq. 1 as a stack of n_layers blocks over one pack:
- * sc_block_forward for layer 0 .. n_layers-1 in order (layers[l] holds the
- * weights of layer l), x updated in place, one plan for every layer.  The
- * arguments of every layer are checked before the first launch.  When a
- * launch fails, the pack's states are left unwritten in every layer (x holds
- * a partial result): the caller restores x and runs it again. */
+ * the blocks of layer 0 .. n_layers-1 in order (layers[l] holds the weights
+ * of layer l), x updated in place, one plan for every layer.  The same function
+ * as n_layers calls of sc_block_forward, but not the same bits: a layer without
+ * modulation takes the factors of its first RMSNorm from sums of squares that
+ * the layer before it stored, a block called by itself from a pass over x, and
+ * the two fp32 sums differ in order.  The arguments of every layer are checked
+ * before the first launch.  When a launch fails, the pack's states are left
+ * unwritten in every layer (x holds a partial result): the caller restores x
+ * and runs it again. */
 int sc_stack_forward(const sc_block_weights* layers, int32_t n_layers, sc_cache* cache,
                      const sc_plan* plan, void* x, const sc_rope* rope, void* ws, size_t ws_bytes,
                      sc_stream stream);

@@ -65,8 +65,10 @@ class StackPipeline:
         forward layer by layer: it is called with phase "in" before and "out"
         after each layer's block is enqueued (x: the pack's activations,
         layers: the block weights in use).  The layers then run one
-        sc_block_forward call each instead of one sc_stack_forward call;
-        the work is the same."""
+        sc_block_forward call each instead of one sc_stack_forward call:
+        the same function of the inputs, equal up to the order of fp32 sums
+        (a stack takes its layers' first RMSNorm factors from sums that the
+        layer before stored)."""
         n = self.n_tok
         sel = sc.sc_selection_build(self.policy, self.K, self.W, nodes)
         plan = sc.sc_plan_build(sel, self.cache)
