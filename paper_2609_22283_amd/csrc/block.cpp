@@ -347,6 +347,9 @@ extern "C" int sc_block_forward(const sc_block_weights* w, sc_cache* c, int32_t 
   return rc != SC_OK ? rc : block_forward(w, c, layer, p, x, rope, ws, false, nullptr, stream);
 }
 
+// The sums of squares of the key norm, at the start; the rest held the projected
+// rows before they went straight into the pages, and stays asked for so that the
+// size a caller was told does not change.
 extern "C" size_t sc_condition_workspace_bytes(const sc_cache* c) {
   if (!c) return 0;
   const size_t L = (size_t)c->d.tokens_per_page * c->d.pages_per_chunk;

@@ -185,45 +185,38 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FB][TB], const EpiPre
     }
     // v is stored transposed per page ([head][d][token]).  Each wave stages
     // its v tile in its own LDS region (free after the main loop; rows
-    // padded by 16 bytes against bank conflicts; in two passes of half the
-    // rows where the whole tile does not fit), then each lane writes runs of
+    // padded by 16 bytes against bank conflicts), then each lane writes runs of
     // 8 consecutive tokens of one feature row as 16-byte stores.  Pages hold
     // a multiple of 8 tokens (so do nodes), so no run crosses a page.
     if (sec == 2) {
       constexpr int LDSW = GWN + 8;  // staged row length (elements)
-      constexpr int RP = WM * LDSW * 2 <= LDSB ? WM : WM / 2;  // rows per pass
       constexpr int SEGS = GWN / 8;
-      static_assert(RP * LDSW * 2 <= LDSB && (RP * SEGS) % 64 == 0 && RP % 16 == 0,
-                    "v staging layout");
+      static_assert(WM * LDSW * 2 <= LDSB && (WM * SEGS) % 64 == 0, "v staging layout");
       uint16_t* lt = reinterpret_cast<uint16_t*>(lds);
       const int32_t d0 = hf0 - head * ep.head_dim;  // wave's first feature within its head
 #pragma unroll
-      for (int pass = 0; pass < WM / RP; ++pass) {
+      for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-        for (int fb = pass * RP / 16; fb < (pass + 1) * RP / 16; ++fb)
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-          for (int tb = 0; tb < TB; ++tb)
+          for (int e = 0; e < 4; ++e) lt[(16 * fb + 4 * lg + e) * LDSW + 16 * tb + c16] = f32_to_bf16(acc[fb][tb][e]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-              lt[(16 * fb - pass * RP + 4 * lg + e) * LDSW + 16 * tb + c16] = f32_to_bf16(acc[fb][tb][e]);
+      for (int j = 0; j < WM * SEGS / 64; ++j) {
+        const int32_t r = lane + 64 * j, row = r / SEGS, seg = r - row * SEGS;
+        const int32_t t = tw + 8 * seg;
+        if (t >= T) continue;
+        const u32x4 val = *reinterpret_cast<const u32x4*>(lt + row * LDSW + 8 * seg);
+        const int32_t node = (int32_t)fast_div((uint32_t)t, ep.nq_div), tok = t - node * ep.nq;
+        const int32_t frame = (int32_t)fast_div((uint32_t)tok, ep.tpp_div), n = tok - frame * ep.tpp;
+        char* slot_base = ep.layer_base + (size_t)ep.node_slot[node * ep.ppc + frame] * ep.slot_bytes;
+        uint16_t* vrow = reinterpret_cast<uint16_t*>(slot_base + ep.kv_half) +
+                         ((size_t)head * ep.head_dim + d0 + row) * ep.tpp + n;
+        if (t + 8 <= T) {
+          *reinterpret_cast<u32x4u*>(vrow) = val;
+        } else {  // a launch ending inside a run
 #pragma unroll
-        for (int j = 0; j < RP * SEGS / 64; ++j) {
-          const int32_t r = lane + 64 * j, row = r / SEGS, seg = r - row * SEGS;
-          const int32_t t = tw + 8 * seg;
-          if (t >= T) continue;
-          const u32x4 val = *reinterpret_cast<const u32x4*>(lt + row * LDSW + 8 * seg);
-          const int32_t node = (int32_t)fast_div((uint32_t)t, ep.nq_div), tok = t - node * ep.nq;
-          const int32_t frame = (int32_t)fast_div((uint32_t)tok, ep.tpp_div), n = tok - frame * ep.tpp;
-          char* slot_base = ep.layer_base + (size_t)ep.node_slot[node * ep.ppc + frame] * ep.slot_bytes;
-          uint16_t* vrow = reinterpret_cast<uint16_t*>(slot_base + ep.kv_half) +
-                           ((size_t)head * ep.head_dim + d0 + pass * RP + row) * ep.tpp + n;
-          if (t + 8 <= T) {
-            *reinterpret_cast<u32x4u*>(vrow) = val;
-          } else {  // a launch ending inside a run
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (i < T - t) vrow[i] = (uint16_t)(val[i >> 1] >> (16 * (i & 1)));
-          }
+          for (int i = 0; i < 8; ++i)
+            if (i < T - t) vrow[i] = (uint16_t)(val[i >> 1] >> (16 * (i & 1)));
         }
       }
       return;
