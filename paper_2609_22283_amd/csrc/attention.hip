@@ -68,8 +68,8 @@ struct AttnGeom {
 // at few tiles per wave the loads' latency.  The split over waves fills the
 // chip from one node's queries: one thread per query (the form before) had
 // 40 waves in flight and a chain of 128 dependent FMAs per key.
-// 4 nodes x 312 queries x 2184 keys, 2 heads of 128: 59 us (47 TFLOP/s) against
-// 15.6 ms.
+// 4 nodes x 312 queries x 2184 keys, 2 heads of 128: 61 us (46 TFLOP/s; 59 before
+// the values behind a page's end were cleared) against 15.6 ms.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int F32_NW = 8, F32_BQ = 16, F32_BK = 16;
 

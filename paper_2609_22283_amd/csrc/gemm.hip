@@ -23,7 +23,7 @@
 // of one token, so RoPE pairs stay in-lane.
 //
 // What bounds it: at thousands of tokens the matrix cores' issue and the
-// ring's copies (MLP-down at 18720 tokens 1.15 PFLOP/s, 450 us, against 480 us
+// ring's copies (MLP-down at 18720 tokens 1.17 PFLOP/s, 440 us, against 468 us
 // before fragments were read ahead across the stage barrier); at a few
 // hundred tokens the copies' latency and the launch, since the weights are
 // read once.  Before the small tiles and the split, launches of 64 .. 512
