@@ -29,6 +29,7 @@
 // read once.  Before the small tiles and the split, launches of 64 .. 512
 // tokens took 26 - 35 us at 1536 k and 120 us at 8960 k whatever their size (6
 // to 70 work-groups, one 48 KB stage in flight each); now 8 - 20 us.
+#include <algorithm>
 #include <cstring>
 
 #include "device.h"
@@ -680,10 +681,16 @@ static GemmShape gemm_shape(int epi, int32_t F, int32_t T, int32_t Kd, size_t pa
       const double n = (double)((nk + S - 1) / S);
       double cost = c.once + (double)full * (n * c.stage + c.fixed) + (S > 1 ? 3.5 + 0.2e-6 * bytes : 0.0);
       if (rest) cost += rest <= kCUs ? n * c.stage1 + c.fixed1 : n * c.stage + c.fixed;
-      // the QKV epilogue (RoPE, page scatter): 2.5 - 4 us per round where a
-      // CU holds one work-group, once where another's main loop covers it
-      // (64 x 64 tiles, 288 .. 864 work-groups: 3 us in all; two per CU: 1)
-      if (epi == EPI_QKV) cost += c.slots > kCUs ? 1.0 : c.once > 0.0 ? 3.0 : 3.0 * (double)(full + (rest != 0));
+      // the QKV epilogue (RoPE, page scatter): 3 us per round where a CU holds
+      // one work-group, but no more than 8 in all, since work-groups fall out of
+      // step over the rounds (3000 .. 23400 tokens on the four 256-feature and
+      // the deep 128 x 128 tiles, one to thirteen rounds: 3 - 9 us above the
+      // same shape without it; at 3 us for each round, 23400 tokens went to 128
+      // x 128 tiles, 344 us against 337 on 256 x 192); once where another's main
+      // loop covers it (64 x 64 tiles, 288 .. 864 work-groups: 3 us in all; two
+      // per CU: 1)
+      if (epi == EPI_QKV)
+        cost += c.slots > kCUs ? 1.0 : c.once > 0.0 ? 3.0 : std::min(8.0, 3.0 * (double)(full + (rest != 0)));
       if (cost < best_cost - 1e-9) {
         best_cost = cost;
         best = GemmShape{i, S};
