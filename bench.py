@@ -45,8 +45,8 @@ T_SCHEDULE_K4 = (0.0, 5.0 / 8.0, 5.0 / 6.0, 15.0 / 16.0, 1.0)
 # FETCH_SIZE and WRITE_SIZE per dispatch, scaled by what the same counters
 # read for a plain 256 MiB copy (x2.0 fetch, x1.0 write).  Valid only for the
 # kernel sources it was measured on (hash below); otherwise reported as null.
-ATTN_TRAFFIC = {"sources_sha1": "c261a262610c20a9c596a956e8688d36f375a5bb",
-                "fetch_bytes": 1.3516e+09, "write_bytes": 2.0062e+08}
+ATTN_TRAFFIC = {"sources_sha1": "ca91bbc209fdf6d291d49c70fa59fc3f9342e7c1",
+                "fetch_bytes": 1.3514e+09, "write_bytes": 2.0062e+08}
 
 
 def attn_traffic():

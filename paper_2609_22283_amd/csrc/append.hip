@@ -89,9 +89,11 @@ template <> struct Vec<float> {
 // A thread takes one 16-byte run of channels of every (256 / runs per row)th
 // token: all its loads (keys, values, rotations) go out before the first is
 // used.  Keys are rotated and stored as they are; values cross LDS, where the
-// 16-byte token segments of channel row d are XORed with the row's run index so
-// that neither side's lanes meet on a bank, and leave as 16-byte runs of one
-// channel's tokens (pages hold a multiple of 8 tokens, so a run stays in one).
+// 16-byte token segments of channel row d are XORed with the row's run index, and
+// leave as 16-byte runs of one channel's tokens (pages hold a multiple of 8 tokens,
+// so a run stays in one).  The reads meet no bank conflict; of the 2-byte writes,
+// runs r and r + 8 share banks and token pairs a word (conflicts in 44 % of the LDS
+// cycles by the counters, hidden behind memory).
 // Bound by memory: a Wan chunk (57.5 MB read and written) 11.2 us, 5.1 TB/s,
 // against 27.4 for 2-byte accesses; a small page by its chain of latencies.
 template <typename T, int HD, bool ROPE>
